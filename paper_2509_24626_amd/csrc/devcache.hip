@@ -9,88 +9,56 @@
 //      raises the error flag and leaves the unit untouched;
 //   2. hits are looked up in the unit's block table and refresh their last
 //      use; the hit slots are marked in an LDS bitmap;
-//   3. misses, ranked in ascending block order by a workgroup scan, take the
-//      unit's empty slots first (in slot order);
+//   3. misses, ranked in ascending block order, take the unit's empty slots
+//      first (in slot order);
 //   4. the remaining r victims are the r smallest keys (last use, slot) among
 //      the occupied, unmarked slots.  A binary search over last-use values
-//      (slot last uses staged in LDS) finds the threshold T with at least r
-//      keys at or below it; the victims are all keys below T and the lowest
-//      slots at T; each victim's rank among them orders the assignment;
+//      finds the threshold T with at least r keys at or below it; the victims
+//      are all keys below T and the lowest slots at T; each victim's rank
+//      among them orders the assignment;
 //   5. miss q takes empty slot q, or the victim of rank q - empties; the
 //      evicted blocks leave the block table; the unit's miss rows (b, g,
 //      block, slot), in ascending block order, go to the unit's own region
 //      of the miss buffer, with their count.
+//
+// What bounds it is latency: a chain of dependent loads (the unit's bounds,
+// its selection, the table entries) and the exchanges between its waves.  So
+// every load that can be made before its use is certain is made at the start
+// (the last uses of all slots come with the table entries), the last uses
+// stay in registers, and counts and ranks are ballots within a wave with one
+// LDS exchange of the waves' totals and one barrier each: a probe of the
+// binary search is PS compares and a barrier.  Victims are ranked on packed
+// 32-bit (last use, slot) keys read four at a time; last uses that span 2^19
+// steps or more take the two-word comparison.  Miss totals are kept per unit
+// (one word that all units added to cost 0.9 us of 12.6).  192 units with
+// k = 512 and 1024 slots, half of the selection missed, launches back to
+// back: 30.6 us before (last uses in LDS, two barriers and a scan per probe,
+// keys looked up through the slot list in the ranking), 11.7 us now.
+#include <algorithm>
+#include <numeric>
 #include <vector>
 
 #include "internal.hpp"
 
 namespace {
 
-constexpr int NT = 256;
 constexpr int KMAX = 512;         // selections per unit
 constexpr int CMAX = 8192;        // slots per unit
+constexpr int SLOT_BITS = 13;     // CMAX = 2^13
 constexpr int ERR_SELECTION = 1;  // error flag bits
 constexpr int ERR_CAPACITY = 2;
 
-// exclusive scan of one int per thread over the workgroup; returns the prefix, *total gets the sum
-__device__ int block_scan(int v, int *total, int *sm)
+// lanes below this one in `mask`
+__device__ __forceinline__ int lanes_below(unsigned long long mask)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) sm[wave] = x;
-    __syncthreads();
-    int base = 0, sum = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        const int s = sm[w];
-        base += w < wave ? s : 0;
-        sum += s;
-    }
-    __syncthreads();
-    *total = sum;
-    return base + x - v;
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-__device__ int block_sum(int v, int *sm)
-{
-    int t;
-    (void)block_scan(v, &t, sm);
-    return t;
-}
-
-__device__ int block_min(int v, int *sm)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-    if (lane == 0) sm[wave] = v;
-    __syncthreads();
-    int r = sm[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) r = min(r, sm[w]);
-    __syncthreads();
-    return r;
-}
-
-__device__ int block_max(int v, int *sm)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    if (lane == 0) sm[wave] = v;
-    __syncthreads();
-    int r = sm[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) r = max(r, sm[w]);
-    __syncthreads();
-    return r;
-}
-
+// NT threads (NT >= k: thread t owns entry t of the selection), PS slots per
+// thread in registers (NT * PS >= the largest capacity): wave w owns the
+// slots [w*64*PS, (w+1)*64*PS), lane l of it the slots i*64 + l of those, so
+// ranks in slot order are ballots within the wave plus the waves' totals.
+template <int NT, int PS>
 __global__ __launch_bounds__(NT) void resolve_kernel(const int32_t *__restrict__ sel, int k, int32_t step, int u0,
                                                      int Hkv, const int32_t *__restrict__ nblk,
                                                      const int64_t *__restrict__ slot_base,
@@ -100,181 +68,198 @@ __global__ __launch_bounds__(NT) void resolve_kernel(const int32_t *__restrict__
                                                      int32_t *slot_block, int32_t *slot_last, int32_t *block_slot,
                                                      int32_t *__restrict__ slots_out, int32_t *__restrict__ miss_out,
                                                      int32_t *__restrict__ counts, int32_t *err,
-                                                     unsigned long long *total_misses)
+                                                     int64_t *total)
 {
-    __shared__ int32_t s_sel[KMAX], s_hit[KMAX];
-    __shared__ uint32_t s_mark[CMAX / 32];
-    __shared__ int32_t s_last[CMAX];
-    __shared__ int32_t s_vic[KMAX], s_vsorted[KMAX];
-    __shared__ int s_red[NT / 64];
+    constexpr int NW = NT / 64;
+    __shared__ uint32_t s_mark[NT * PS / 32];              // slots hit in this call
+    __shared__ __align__(16) uint32_t s_key[NT + 4];       // victims in slot order: (last use - lo, slot)
+    __shared__ int32_t s_last[NT];                         // their last uses, where those do not fit the key
+    __shared__ int32_t s_sorted[NT];                       // victims by (last use, slot)
+    __shared__ int s_check[NW], s_miss[NW], s_count[2][NW], s_below[NW], s_at[NW];
+    __shared__ uint32_t s_lo[NW], s_hi[NW];
 
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int u = u0 + blockIdx.x;  // absolute unit
     const int b = u / Hkv, g = u - b * Hkv;
-    const int C = cap[u];
-    const int n = min(nblk[b], table_room[b]);
-    const int used_old = used[u];  // read before any barrier: thread 0 rewrites it at the end
     const int32_t *su = sel + (int64_t)blockIdx.x * k;  // rows of this call's units
+    const int32_t j = t < k ? su[t] : -1;
+    const int32_t before = t > 0 && t < k ? su[t - 1] : -1;
+    const int C = min(cap[u], NT * PS);
+    const int n = min(nblk[b], table_room[b]);
+    const int used_old = min(used[u], C);  // read before any barrier: thread 0 rewrites it at the end
+    const int64_t total_old = total[u];
     int32_t *out = slots_out + (int64_t)blockIdx.x * k;
     int32_t *rows = miss_out + (int64_t)u * k * 4;
     int32_t *bs = block_slot + block_base[u];
     int32_t *sb = slot_block + slot_base[u];
     int32_t *sl = slot_last + slot_base[u];
 
+    // last uses of the thread's slots, wanted only if there are evictions:
+    // loaded now, they arrive with the selection's table entries
+    const int s0 = wave * (64 * PS) + lane;
+    uint32_t last[PS];
+#pragma unroll
+    for (int i = 0; i < PS; ++i) last[i] = s0 + i * 64 < used_old ? (uint32_t)sl[s0 + i * 64] : 0xFFFFFFFFu;
+    int32_t hit = j >= 0 && j < n ? bs[j] : -1;
+
     // 1. check the selection
-    int bad = 0, valid = 0;
-    for (int i = t; i < k; i += NT) {
-        const int32_t j = su[i];
-        s_sel[i] = j;
-        if (j < 0) {
-            bad |= j != -1;
-        } else {
-            const int32_t p = i > 0 ? su[i - 1] : -1;
-            bad |= (i > 0 && (p < 0 || p >= j)) || j >= n;
-            ++valid;
-        }
-    }
-    for (int i = t; i < CMAX / 32; i += NT) s_mark[i] = 0u;
-    bad = block_sum(bad, s_red);
-    valid = block_sum(valid, s_red);
-    if (bad || valid > C) {
-        for (int i = t; i < k; i += NT) out[i] = -1;
+    for (int i = t; i < NT * PS / 32; i += NT) s_mark[i] = 0u;
+    const bool bad_t = j < 0 ? (j != -1) : (j >= n || (t > 0 && (before < 0 || before >= j)));
+    const int check = __popcll(__ballot(j >= 0)) | (__ballot(bad_t) ? 1 << 16 : 0);
+    if (lane == 0) s_check[wave] = check;
+    __syncthreads();
+    int valid = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) valid += s_check[w];
+    if (valid > C) {  // a malformed selection counts 2^16 per wave that saw it
+        if (t < k) out[t] = -1;
         if (t == 0) {
             counts[u] = 0;
-            atomicOr(err, bad ? ERR_SELECTION : ERR_CAPACITY);
+            atomicOr(err, (valid >> 16) ? ERR_SELECTION : ERR_CAPACITY);
         }
         return;
     }
 
-    // 2. hits
-    for (int i = t; i < k; i += NT) {
-        const int32_t j = s_sel[i];
-        int32_t s = -1;
-        if (j >= 0) {
-            s = bs[j];
-            if (s >= 0) atomicOr(&s_mark[s >> 5], 1u << (s & 31));
-        }
-        s_hit[i] = s;
-    }
+    // 2., 3. mark the hits; rank the misses in entry (ascending block) order
+    if (hit >= 0) atomicOr(&s_mark[hit >> 5], 1u << (hit & 31));
+    const bool is_miss = j >= 0 && hit < 0;
+    const unsigned long long miss_mask = __ballot(is_miss);
+    if (lane == 0) s_miss[wave] = __popcll(miss_mask);
     __syncthreads();
-
-    // 3. miss ranks in selection (ascending block) order: each thread owns a
-    //    contiguous run of entries so the scan keeps that order
-    constexpr int PER = KMAX / NT;  // 2
-    int flags[PER], local = 0;
+    int m = 0, q = lanes_below(miss_mask);
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int i = t * PER + e;
-        flags[e] = (i < k && s_sel[i] >= 0 && s_hit[i] < 0) ? 1 : 0;
-        local += flags[e];
+    for (int w = 0; w < NW; ++w) {
+        const int c = s_miss[w];
+        m += c;
+        q += w < wave ? c : 0;
     }
-    int m;
-    const int base = block_scan(local, &m, s_red);
     const int empties = min(m, C - used_old);
     const int r = m - empties;  // evictions
 
     // 4. victims: the r smallest (last use, slot) among occupied, unmarked slots
     if (r > 0) {
-        for (int s = t; s < used_old; s += NT) s_last[s] = sl[s];
-        __syncthreads();
-        auto cand = [&](int s) { return ((s_mark[s >> 5] >> (s & 31)) & 1u) == 0u; };
-        int lo = INT32_MAX, hi = -1;  // occupied slots have last uses >= 0
-        for (int s = t; s < used_old; s += NT)
-            if (cand(s)) {
-                lo = min(lo, s_last[s]);
-                hi = max(hi, s_last[s]);
-            }
-        lo = block_min(lo, s_red);
-        hi = block_max(hi, s_red);
-        // smallest T in [lo, hi] with count(last <= T) >= r
-        while (lo < hi) {
-            const int mid = lo + (int)(((int64_t)hi - lo) >> 1);
-            int c = 0;
-            for (int s = t; s < used_old; s += NT) c += (cand(s) && s_last[s] <= mid) ? 1 : 0;
-            c = block_sum(c, s_red);
-            if (c >= r) hi = mid;
-            else lo = mid + 1;
+        uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+        for (int i = 0; i < PS; ++i) {
+            const int s = s0 + i * 64;
+            if ((s_mark[s >> 5] >> (s & 31)) & 1u) last[i] = 0xFFFFFFFFu;  // not a candidate, above every last use
+            lo = min(lo, last[i]);
+            hi = max(hi, last[i] == 0xFFFFFFFFu ? 0u : last[i]);
         }
-        const int T = lo;
-        int below = 0;
-        for (int s = t; s < used_old; s += NT) below += (cand(s) && s_last[s] < T) ? 1 : 0;
-        below = block_sum(below, s_red);
-        const int need_at = r - below;  // lowest slots with last use T
-        // victims in slot order: each thread owns a contiguous run of slots
-        const int per = (used_old + NT - 1) / NT;
-        const int s0 = t * per, s1 = min(used_old, s0 + per);
-        int at = 0, vic = 0;
-        for (int s = s0; s < s1; ++s)
-            if (cand(s) && s_last[s] == T) ++at;
-        int at_total;
-        int at_rank = block_scan(at, &at_total, s_red);
-        for (int s = s0; s < s1; ++s)
-            if (cand(s)) {
-                if (s_last[s] < T) ++vic;
-                else if (s_last[s] == T && at_rank++ < need_at) ++vic;
-            }
-        int vic_total;
-        int vpos = block_scan(vic, &vic_total, s_red);
-        at_rank = block_scan(at, &at_total, s_red);  // recount for the second pass
-        for (int s = s0; s < s1; ++s)
-            if (cand(s)) {
-                bool take = false;
-                if (s_last[s] < T) take = true;
-                else if (s_last[s] == T && at_rank++ < need_at) take = true;
-                if (take) s_vic[vpos++] = s;
-            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
+        }
+        if (lane == 0) {
+            s_lo[wave] = lo;
+            s_hi[wave] = hi;
+        }
         __syncthreads();
-        // rank of each victim by (last use, slot)
-        for (int i = t; i < r; i += NT) {
-            const int v = s_vic[i];
-            const int lv = s_last[v];
-            int rank = 0;
-            for (int w = 0; w < r; ++w) {
-                const int x = s_vic[w];
-                const int lx = s_last[x];
-                rank += (lx < lv || (lx == lv && x < v)) ? 1 : 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            lo = min(lo, s_lo[w]);
+            hi = max(hi, s_hi[w]);
+        }
+        // smallest T in [lo, hi] with count(last <= T) >= r.  The counts
+        // alternate between two buffers, so one barrier per probe is enough.
+        uint32_t T = lo;
+        for (int p = 0; T < hi; p ^= 1) {
+            const uint32_t mid = T + ((hi - T) >> 1);
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < PS; ++i) c += __popcll(__ballot(last[i] <= mid));
+            if (lane == 0) s_count[p][wave] = c;
+            __syncthreads();
+            c = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) c += s_count[p][w];
+            if (c >= r) hi = mid;
+            else T = mid + 1;
+        }
+        // all candidates below T, then the lowest slots at T
+        int below = 0, at = 0;
+#pragma unroll
+        for (int i = 0; i < PS; ++i) {
+            below += __popcll(__ballot(last[i] < T));
+            at += __popcll(__ballot(last[i] == T));
+        }
+        if (lane == 0) {
+            s_below[wave] = below;
+            s_at[wave] = at;
+        }
+        __syncthreads();
+        int need = r;  // candidates at T that go
+#pragma unroll
+        for (int w = 0; w < NW; ++w) need -= s_below[w];
+        int pos = 0, at_rank = 0;  // victims, and candidates at T, in the waves before this one
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            if (w < wave) {
+                pos += s_below[w] + min(s_at[w], max(0, need - at_rank));
+                at_rank += s_at[w];
             }
-            s_vsorted[rank] = v;
+        const bool narrow = T - lo < (1u << (32 - SLOT_BITS));
+#pragma unroll
+        for (int i = 0; i < PS; ++i) {
+            const unsigned long long at_mask = __ballot(last[i] == T);
+            const bool take = last[i] < T || (last[i] == T && at_rank + lanes_below(at_mask) < need);
+            const unsigned long long take_mask = __ballot(take);
+            if (take) {
+                const int at_pos = pos + lanes_below(take_mask);
+                s_key[at_pos] = narrow ? (last[i] - lo) << SLOT_BITS | (uint32_t)(s0 + i * 64) : (uint32_t)(s0 + i * 64);
+                s_last[at_pos] = (int32_t)last[i];
+            }
+            at_rank += __popcll(at_mask);
+            pos += __popcll(take_mask);
+        }
+        if (t < 4) s_key[r + t] = 0xFFFFFFFFu;  // the rank loop reads four keys at a time
+        __syncthreads();
+        if (t < r) {
+            const uint32_t v = s_key[t];
+            int rank = t;  // slot order is the order where all last uses are one
+            if (T != lo && narrow) {
+                rank = 0;
+                for (int w = 0; w < r; w += 4) {
+                    const uint4 x = *reinterpret_cast<const uint4 *>(s_key + w);
+                    rank += (x.x < v) + (x.y < v) + (x.z < v) + (x.w < v);
+                }
+            } else if (T != lo) {
+                const int32_t lv = s_last[t];
+                rank = 0;
+                for (int w = 0; w < r; ++w) rank += s_last[w] < lv || (s_last[w] == lv && w < t);
+            }
+            s_sorted[rank] = (int32_t)(v & (CMAX - 1));
         }
         __syncthreads();
     }
 
     // 5. assignment and state updates
-    int q = base;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int i = t * PER + e;
-        if (i >= k) continue;
-        const int32_t j = s_sel[i];
-        if (j < 0) {
-            out[i] = -1;
-        } else if (s_hit[i] >= 0) {
-            out[i] = s_hit[i];
-            sl[s_hit[i]] = step;
-        } else {
-            int32_t s;
+    if (t < k) {
+        int32_t s = hit;
+        if (is_miss) {
             if (q < empties) {
                 s = used_old + q;
             } else {
-                s = s_vsorted[q - empties];
+                s = s_sorted[q - empties];
                 bs[sb[s]] = -1;  // the evicted block leaves the table
             }
             sb[s] = j;
             bs[j] = s;
-            sl[s] = step;
-            out[i] = s;
             int32_t *row = rows + 4 * q;
             row[0] = b;
             row[1] = g;
             row[2] = j;
             row[3] = s;
-            ++q;
         }
+        if (j >= 0) sl[s] = step;
+        out[t] = j >= 0 ? s : -1;
     }
     if (t == 0) {
         used[u] = used_old + empties;
         counts[u] = m;
-        atomicAdd(total_misses, (unsigned long long)m);
+        total[u] = total_old + m;
     }
 }
 
@@ -284,13 +269,38 @@ struct ss_dev_cache {
     int B = 0, Hkv = 0, units = 0;
     int64_t total_slots = 0, total_table = 0;
     int64_t last_step = INT64_MIN;
-    std::vector<int32_t> cap_host;
+    int max_cap = 0;  // largest capacity of any unit
     void *mem = nullptr;  // one device allocation holding every array below
     int64_t *slot_base = nullptr, *block_base = nullptr;
+    int64_t *total = nullptr;  // per unit: misses over all resolves
     int32_t *cap = nullptr, *room = nullptr, *used = nullptr, *counts = nullptr, *err = nullptr;
     int32_t *slot_block = nullptr, *slot_last = nullptr, *block_slot = nullptr;
-    unsigned long long *total = nullptr;  // misses over all resolves
 };
+
+namespace {
+
+template <int NT, int PS>
+void launch_resolve(ss_dev_cache *c, int64_t step, int u0, int units, const int32_t *sel, int k, const int32_t *nblk,
+                    int32_t *slots, int32_t *miss, hipStream_t s)
+{
+    ss::launch(resolve_kernel<NT, PS>, dim3(units), dim3(NT), s, sel, k, (int32_t)step, u0, c->Hkv, nblk, c->slot_base,
+               c->block_base, c->cap, c->room, c->used, c->slot_block, c->slot_last, c->block_slot, slots, miss,
+               c->counts, c->err, c->total);
+}
+
+// threads for k entries, then slots per thread for the largest region
+template <int NT>
+void launch_by_capacity(ss_dev_cache *c, int64_t step, int u0, int units, const int32_t *sel, int k,
+                        const int32_t *nblk, int32_t *slots, int32_t *miss, hipStream_t s)
+{
+    const int per = (c->max_cap + NT - 1) / NT;
+    if (per <= 2) launch_resolve<NT, 2>(c, step, u0, units, sel, k, nblk, slots, miss, s);
+    else if (per <= 4) launch_resolve<NT, 4>(c, step, u0, units, sel, k, nblk, slots, miss, s);
+    else if (per <= 8) launch_resolve<NT, 8>(c, step, u0, units, sel, k, nblk, slots, miss, s);
+    else launch_resolve<NT, CMAX / NT>(c, step, u0, units, sel, k, nblk, slots, miss, s);
+}
+
+}  // namespace
 
 namespace ss {
 int32_t *dev_cache_counts(ss_dev_cache *c) { return c->counts; }
@@ -302,9 +312,8 @@ ss_status dev_cache_launch(ss_dev_cache *c, int64_t step, int b_begin, int b_end
 {
     const int units = (b_end - b_begin) * c->Hkv;
     if (units == 0) return SS_OK;
-    ss::launch(resolve_kernel, dim3(units), dim3(NT), s, sel, k, (int32_t)step, b_begin * c->Hkv, c->Hkv, nblk,
-               c->slot_base, c->block_base, c->cap, c->room, c->used, c->slot_block, c->slot_last, c->block_slot,
-               slots, miss, c->counts, c->err, c->total);
+    if (k <= 256) launch_by_capacity<256>(c, step, b_begin * c->Hkv, units, sel, k, nblk, slots, miss, s);
+    else launch_by_capacity<KMAX>(c, step, b_begin * c->Hkv, units, sel, k, nblk, slots, miss, s);
     return check_launch("ss_dev_cache_resolve");
 }
 
@@ -348,10 +357,10 @@ ss_status ss_dev_cache_create(int B, int Hkv, const int32_t *table_room, const i
     c->units = units;
     c->total_slots = slots;
     c->total_table = table;
-    c->cap_host.assign(capacity, capacity + units);
-    // layout: 2 int64 arrays [units]; int32 arrays cap, used, counts [units], room [B], err [1];
+    c->max_cap = *std::max_element(capacity, capacity + units);
+    // layout: 3 int64 arrays [units]; int32 arrays cap, used, counts [units], room [B], err [1];
     // slot_block, slot_last [slots]; block_slot [table]
-    const size_t bytes = 8 + 16 * (size_t)units + 4 * (3 * (size_t)units + B + 1) + 8 * (size_t)slots +
+    const size_t bytes = 24 * (size_t)units + 4 * (3 * (size_t)units + B + 1) + 8 * (size_t)slots +
                          4 * (size_t)table + 64;
     hipError_t e = hipMalloc(&c->mem, bytes);
     if (e != hipSuccess) {
@@ -360,9 +369,8 @@ ss_status ss_dev_cache_create(int B, int Hkv, const int32_t *table_room, const i
         return ss::fail(SS_ERR_OOM, "ss_dev_cache_create: hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
     }
     char *p = static_cast<char *>(c->mem);
-    c->total = reinterpret_cast<unsigned long long *>(p);
-    p += 8;
-    c->slot_base = reinterpret_cast<int64_t *>(p);
+    c->total = reinterpret_cast<int64_t *>(p);
+    c->slot_base = c->total + units;
     c->block_base = c->slot_base + units;
     c->cap = reinterpret_cast<int32_t *>(c->block_base + units);
     c->used = c->cap + units;
@@ -382,7 +390,7 @@ ss_status ss_dev_cache_create(int B, int Hkv, const int32_t *table_room, const i
     if (e == hipSuccess) e = hipMemcpyAsync(c->counts, zeros.data(), 4 * (size_t)units, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(c->room, room.data(), 4 * (size_t)B, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemsetAsync(c->err, 0, 4, s);
-    if (e == hipSuccess) e = hipMemsetAsync(c->total, 0, 8, s);
+    if (e == hipSuccess) e = hipMemsetAsync(c->total, 0, 8 * (size_t)units, s);
     if (e == hipSuccess) e = hipMemsetAsync(c->slot_block, 0xFF, 4 * (size_t)slots, s);  // -1: empty
     if (e == hipSuccess) e = hipMemsetAsync(c->slot_last, 0xFF, 4 * (size_t)slots, s);
     if (e == hipSuccess) e = hipMemsetAsync(c->block_slot, 0xFF, 4 * (size_t)table, s);  // -1: not cached
@@ -445,11 +453,16 @@ int64_t ss_dev_cache_total_slots(const ss_dev_cache *c) { return c ? c->total_sl
 ss_status ss_dev_cache_total_misses(const ss_dev_cache *c, int64_t *total)
 {
     SS_CHECK_ARG(c && total, "ss_dev_cache_total_misses: null pointer");
-    unsigned long long v = 0;
+    std::vector<int64_t> per_unit;
+    try {
+        per_unit.resize(c->units);
+    } catch (const std::bad_alloc &) {
+        return ss::fail(SS_ERR_OOM, "ss_dev_cache_total_misses: out of memory");
+    }
     hipError_t e = hipDeviceSynchronize();
-    if (e == hipSuccess) e = hipMemcpy(&v, c->total, 8, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(per_unit.data(), c->total, 8 * per_unit.size(), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return ss::fail(SS_ERR_HIP, "ss_dev_cache_total_misses: %s", hipGetErrorString(e));
-    *total = (int64_t)v;
+    *total = std::accumulate(per_unit.begin(), per_unit.end(), (int64_t)0);
     return SS_OK;
 }
 

@@ -155,3 +155,17 @@ def test_rejects_unsupported_sizes(ss):
             ss.ss_dev_cache_resolve(h, 0, 0, 1, z, 513, z, z, z)
     finally:
         ss.ss_dev_cache_destroy(h)
+
+
+@pytest.mark.parametrize("k,cap,far", [(1, 1, False), (64, 70, True), (256, 512, False), (256, 513, True),
+                                       (257, 1024, False), (300, 1025, True), (200, 2049, False), (512, 4097, True)])
+def test_edges_of_the_launch_shapes(ss, oracle_impl, k, cap, far):
+    """Either side of the thread counts (k = 256, 257) and of the slots held
+    per thread; `far` spreads the last uses over more than 2^19 steps, past
+    what the victims' packed keys hold, with several of them in one call."""
+    nblk = np.array([4 * cap + 3, max(k, cap - 1), 2 * cap], np.int32)
+    caps = np.repeat(np.minimum(nblk, cap), 2).astype(np.int32)
+    steps = 6 + 4 * cap // k
+    ids = [s * 1000003 for s in range(steps)] if far else None
+    print(f"[gpu] device resolve, k {k}, {cap} slots, far {far}", flush=True)
+    run_stream(ss, oracle_impl, nblk, 2, k, caps, steps, 0.7, seed=k + cap, step_ids=ids)
