@@ -2,154 +2,223 @@
 // bounding cuboid (channel-wise min and max) of the keys of each KV block,
 // or, as the mean-key variant, the mean of the block's keys.
 //
-// Cuboids: one wave per 64/blk consecutive block records.  A K tile is blk
-// rows of 128 bf16 channels (256 B per row); each lane loads 16 B (8
-// channels) of one row per step, so one wave-wide load covers 4 rows, and
-// all 16 loads of the wave's records are issued before any is reduced (a
-// wave per single record kept too few bytes in flight).  Min and max run on
-// 16-bit totalOrder keys, two channels per 32-bit word, then across the four
-// row groups of the wave.  Lanes 0..15 write lo and hi.
+// HBM bounds it: each key is read once, and little is written.  A wave owns
+// up to 8 consecutive blocks of one unit and issues all of its loads (16 KiB
+// for cuboids) before it reduces anything.  Keys that cannot still lie in the
+// 256 MB last-level cache (more than kLargeBytes of them) are read with the
+// non-temporal policy, and with the heads' waves side by side where the
+// heads' rows are interleaved (place(), below).  A layer of a 128k-token
+// prompt (token-major, 8 heads, 302 MB moved): cuboids 77.5 us before, 61.2
+// with the default policy, 53.4 with both (5.66 TB/s); mean keys 67.7, 53.5
+// and 47.6 us.  128k tokens as block records: 61.3 and 50.9 us, mean keys
+// 49.5 and 45.9.  Within the cache both cost time: 33 MB of keys in blocks of
+// 8 took 15.0 us without them and 16.2 to 18.6 with the non-temporal policy,
+// and the mean keys of 67 MB in blocks of 32 took 12.0 us unit by unit and
+// 13.0 with the heads side by side.
 #include "internal.hpp"
 
 namespace {
 
-// bf16 bits -> 16-bit key with unsigned order equal to IEEE totalOrder,
-// two lanes per word: negative values flip all bits, others set the sign.
-__device__ __forceinline__ uint32_t to_key2(uint32_t w)
-{
-    uint32_t s = (w >> 15) & 0x00010001u;
-    return w ^ (0x80008000u | (s * 0x7FFFu));
-}
+constexpr int D = ss::kHeadDim;
+constexpr int WAVES = 4;
+constexpr int64_t kLargeBytes = 160LL << 20;  // slower at 128 MiB of keys, faster at 192
 
-__device__ __forceinline__ uint32_t from_key2(uint32_t k)
-{
-    uint32_t s = (k >> 15) & 0x00010001u;  // set for non-negative values
-    return k ^ (0xFFFFFFFFu ^ (s * 0x7FFFu));
-}
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+typedef short i16x2_t __attribute__((ext_vector_type(2)));
 
-typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+// two bf16 values -> two 16-bit keys whose signed order is IEEE totalOrder
+// (-0 < +0): negative values flip their magnitude bits.  Its own inverse.
+__device__ __forceinline__ uint32_t key2(uint32_t w)
+{
+    const i16x2_t sign = __builtin_bit_cast(i16x2_t, w) >> 15;
+    return w ^ (__builtin_bit_cast(uint32_t, sign) & 0x7FFF7FFFu);
+}
 
 __device__ __forceinline__ uint32_t min2(uint32_t a, uint32_t b)
 {
-    u16x2_t r = __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b));
-    return __builtin_bit_cast(uint32_t, r);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(i16x2_t, a),
+                                                                  __builtin_bit_cast(i16x2_t, b)));
 }
 
-__device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b)
+// lanes 0..31: the minimum of a over its two halves, lanes 32..63: that of b
+__device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b)
 {
-    u16x2_t r = __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b));
-    return __builtin_bit_cast(uint32_t, r);
+    const auto x = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    return min2(x[0], x[1]);
 }
 
-template <int BLK>
-__global__ __launch_bounds__(256) void meta_kernel(const uint8_t *__restrict__ kv_base,
-                                                   const int64_t *__restrict__ unit_off,
-                                                   const int32_t *__restrict__ nblk, int Hkv, int nblk_max,
-                                                   int64_t total_blocks, int64_t block_stride, int64_t row_stride,
-                                                   uint16_t *__restrict__ meta)
+// per 32 lanes: the first 16 hold the minimum of a over its two 16-lane rows, the others that of b
+__device__ __forceinline__ uint32_t min_rows(uint32_t a, uint32_t b)
 {
-    constexpr int D = ss::kHeadDim;
-    constexpr int BPW = 64 / BLK;  // block records per wave: 16 loads of 16 B per lane in flight
+    const auto x = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    return min2(x[0], x[1]);
+}
+
+template <bool STREAM, class T>
+__device__ __forceinline__ T load(const T *p)
+{
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+
+struct place_t {
+    int64_t u;  // unit
+    int j0, n;  // first block of the wave, blocks of the unit
+};
+
+// Wave -> `per` consecutive blocks of a unit.  Where a unit's keys lie on
+// their own the waves walk unit after unit; where the heads' rows are
+// interleaved (token-major KV) and come from HBM, neighbouring waves take the
+// heads of the same blocks, so that together they read whole tokens: one head
+// at a time, all reads in flight fall on the same 256 bytes of every token,
+// which are few of the memory channels.
+__device__ __forceinline__ place_t place(int64_t wave, int per, const int32_t *nblk, int Hkv, int nblk_max,
+                                         int heads_inner)
+{
+    const int groups = (nblk_max + per - 1) / per;
+    place_t p;
+    int64_t grp;
+    if (heads_inner) {
+        const int64_t x = wave / Hkv;
+        const int64_t b = x / groups;
+        p.u = b * Hkv + (wave - x * Hkv);
+        grp = x - b * groups;
+    } else {
+        p.u = wave / groups;
+        grp = wave - p.u * groups;
+    }
+    p.j0 = (int)grp * per;
+    const int n = nblk[p.u / Hkv];
+    p.n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
+    return p;
+}
+
+// Cuboids.  A lane loads 16 B (8 channels) of one row per step, so a
+// wave-wide load covers 4 rows, and reduces its rows of each block; the four
+// 16-lane rows then exchange halves instead of all reducing everything: with
+// four blocks, lane row r ends with block r of them.  The largest key is
+// found as the complement of the smallest complement, so every step is one
+// packed minimum.
+template <int BLK, bool STREAM>
+__global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restrict__ kv_base,
+                                                          const int64_t *__restrict__ unit_off,
+                                                          const int32_t *__restrict__ nblk, int Hkv, int nblk_max,
+                                                          int64_t waves, int heads_inner, int64_t block_stride,
+                                                          int64_t row_stride, uint16_t *__restrict__ meta)
+{
+    constexpr int BPW = 64 / BLK;  // blocks per wave: 16 loads of 16 B per lane in flight
     constexpr int LPB = BLK / 4;   // wave-wide loads per K tile (4 rows each)
     const int lane = threadIdx.x & 63;
-    const int64_t id0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * BPW;
-    const int row0 = lane >> 4;          // 0..3
-    const int cbyte = (lane & 15) * 16;  // 8 channels
+    const int64_t w = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= waves) return;
+    const place_t p = place(w, BPW, nblk, Hkv, nblk_max, heads_inner);
+    if (p.j0 >= p.n) return;
+    const int row = lane >> 4, c16 = lane & 15;
+    const uint8_t *src = kv_base + unit_off[p.u] + row * row_stride + c16 * 16;
 
-    // issue every load of the wave's records before reducing any of them
-    uint4 v[BPW][LPB];
-    bool live[BPW];
-    int64_t u_of[BPW];
-    int j_of[BPW];
+    u32x4_t v[BPW][LPB];
 #pragma unroll
     for (int b = 0; b < BPW; ++b) {
-        const int64_t id = id0 + b;  // wave-uniform
-        live[b] = id < total_blocks;
-        u_of[b] = 0;
-        j_of[b] = 0;
-        if (live[b]) {
-            const int64_t u = id / nblk_max;
-            const int j = (int)(id - u * nblk_max);
-            int n = nblk[u / Hkv];
-            n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
-            live[b] = j < n;
-            u_of[b] = u;
-            j_of[b] = j;
-        }
-        if (live[b]) {
-            const uint8_t *rec = kv_base + unit_off[u_of[b]] + (int64_t)j_of[b] * block_stride;
+        const int j = min(p.j0 + b, p.n - 1);  // past the end: the last block again, not stored
 #pragma unroll
-            for (int r = 0; r < LPB; ++r)
-                v[b][r] = *reinterpret_cast<const uint4 *>(rec + (4 * r + row0) * row_stride + cbyte);
-        }
+        for (int r = 0; r < LPB; ++r)
+            v[b][r] = load<STREAM>(reinterpret_cast<const u32x4_t *>(src + j * block_stride + 4 * r * row_stride));
     }
+    uint32_t lo[BPW][4], nhi[BPW][4];  // nhi: complements of the largest keys
 #pragma unroll
-    for (int b = 0; b < BPW; ++b) {
-        if (!live[b]) continue;
-        uint32_t lo[4], hi[4];
-        lo[0] = hi[0] = to_key2(v[b][0].x);
-        lo[1] = hi[1] = to_key2(v[b][0].y);
-        lo[2] = hi[2] = to_key2(v[b][0].z);
-        lo[3] = hi[3] = to_key2(v[b][0].w);
+    for (int b = 0; b < BPW; ++b)
 #pragma unroll
-        for (int r = 1; r < LPB; ++r) {
-            const uint32_t k0 = to_key2(v[b][r].x), k1 = to_key2(v[b][r].y), k2 = to_key2(v[b][r].z),
-                           k3 = to_key2(v[b][r].w);
-            lo[0] = min2(lo[0], k0); hi[0] = max2(hi[0], k0);
-            lo[1] = min2(lo[1], k1); hi[1] = max2(hi[1], k1);
-            lo[2] = min2(lo[2], k2); hi[2] = max2(hi[2], k2);
-            lo[3] = min2(lo[3], k3); hi[3] = max2(hi[3], k3);
-        }
+        for (int i = 0; i < 4; ++i) {
+            lo[b][i] = key2(v[b][0][i]);
+            nhi[b][i] = ~lo[b][i];
 #pragma unroll
-        for (int x = 16; x <= 32; x <<= 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                lo[i] = min2(lo[i], (uint32_t)__shfl_xor((int)lo[i], x));
-                hi[i] = max2(hi[i], (uint32_t)__shfl_xor((int)hi[i], x));
+            for (int r = 1; r < LPB; ++r) {
+                const uint32_t k = key2(v[b][r][i]);
+                lo[b][i] = min2(lo[b][i], k);
+                nhi[b][i] = min2(nhi[b][i], ~k);
             }
         }
-        if (lane < 16) {
-            uint16_t *m = meta + ((int64_t)u_of[b] * nblk_max + j_of[b]) * (2 * D);
-            const uint4 l4 = make_uint4(from_key2(lo[0]), from_key2(lo[1]), from_key2(lo[2]), from_key2(lo[3]));
-            const uint4 h4 = make_uint4(from_key2(hi[0]), from_key2(hi[1]), from_key2(hi[2]), from_key2(hi[3]));
-            *reinterpret_cast<uint4 *>(m + lane * 8) = l4;
-            *reinterpret_cast<uint4 *>(m + D + lane * 8) = h4;
+    uint16_t *m = meta + (p.u * nblk_max + p.j0) * (2 * D) + c16 * 8;
+    if constexpr (BPW == 2) {
+        // lane rows 0, 1: lo and hi of the first block, rows 2, 3: of the second
+        uint4 x;
+        uint32_t *xs = &x.x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t k = min_rows(min_halves(lo[0][i], lo[1][i]), min_halves(nhi[0][i], nhi[1][i]));
+            xs[i] = key2(row & 1 ? ~k : k);
+        }
+        if (p.j0 + (row >> 1) < p.n) *reinterpret_cast<uint4 *>(m + row * D) = x;
+    } else {
+#pragma unroll
+        for (int b = 0; b < BPW; b += 4) {
+            uint4 x, y;
+            uint32_t *xs = &x.x, *ys = &y.x;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                xs[i] = key2(min_rows(min_halves(lo[b][i], lo[b + 2][i]), min_halves(lo[b + 1][i], lo[b + 3][i])));
+                ys[i] = key2(~min_rows(min_halves(nhi[b][i], nhi[b + 2][i]),
+                                       min_halves(nhi[b + 1][i], nhi[b + 3][i])));
+            }
+            if (p.j0 + b + row < p.n) {
+                *reinterpret_cast<uint4 *>(m + (b + row) * (2 * D)) = x;
+                *reinterpret_cast<uint4 *>(m + (b + row) * (2 * D) + D) = y;
+            }
         }
     }
 }
 
-// Mean key of each block: one wave per block record, each lane two
-// channels; rows are summed in fp64 in token order (each wave-wide load is
-// one contiguous 256-byte row; the sum of blk bf16 keys is exact unless
+// Mean key of each block: one wave per block, each lane two channels (with
+// two blocks per wave and four channels per lane the mean keys of 128k tokens
+// in blocks of 16 took 48.2 to 49.7 us against 47.6 and 45.9); the rows are
+// summed in fp64 in token order (the sum of blk bf16 keys is exact unless
 // their magnitudes span more than about 2^40), scaled by 1/blk (exact) and
 // rounded once to bf16, ties to even.
-template <int BLK>
-__global__ __launch_bounds__(256) void meta_mean_kernel(const uint8_t *__restrict__ kv_base,
-                                                        const int64_t *__restrict__ unit_off,
-                                                        const int32_t *__restrict__ nblk, int Hkv, int nblk_max,
-                                                        int64_t total_blocks, int64_t block_stride,
-                                                        int64_t row_stride, uint32_t *__restrict__ meta)
+template <int BLK, bool STREAM>
+__global__ __launch_bounds__(WAVES * 64) void meta_mean_kernel(const uint8_t *__restrict__ kv_base,
+                                                               const int64_t *__restrict__ unit_off,
+                                                               const int32_t *__restrict__ nblk, int Hkv,
+                                                               int nblk_max, int64_t waves, int heads_inner,
+                                                               int64_t block_stride, int64_t row_stride,
+                                                               uint16_t *__restrict__ meta)
 {
-    constexpr int D = ss::kHeadDim;
     const int lane = threadIdx.x & 63;
-    const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (id >= total_blocks) return;
-    const int64_t u = id / nblk_max;
-    const int j = (int)(id - u * nblk_max);
-    int n = nblk[u / Hkv];
-    n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
-    if (j >= n) return;
-    const uint8_t *rec = kv_base + unit_off[u] + (int64_t)j * block_stride;
-    uint32_t w[BLK];
+    const int64_t w = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= waves) return;
+    const place_t p = place(w, 1, nblk, Hkv, nblk_max, heads_inner);
+    if (p.j0 >= p.n) return;
+    const uint8_t *src = kv_base + unit_off[p.u] + p.j0 * block_stride + lane * 4;
+
+    uint32_t v[BLK];
 #pragma unroll
-    for (int t = 0; t < BLK; ++t) w[t] = reinterpret_cast<const uint32_t *>(rec + t * row_stride)[lane];
+    for (int t = 0; t < BLK; ++t) v[t] = load<STREAM>(reinterpret_cast<const uint32_t *>(src + t * row_stride));
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int t = 0; t < BLK; ++t) {
-        s0 = s0 + (double)__uint_as_float(w[t] << 16);
-        s1 = s1 + (double)__uint_as_float(w[t] & 0xFFFF0000u);
+        s0 += (double)__uint_as_float(v[t] << 16);
+        s1 += (double)__uint_as_float(v[t] & 0xFFFF0000u);
     }
-    meta[(u * nblk_max + j) * (D / 2) + lane] = ss::pack_bf16_rne_f64(s0 * (1.0 / BLK), s1 * (1.0 / BLK));
+    reinterpret_cast<uint32_t *>(meta + (p.u * nblk_max + p.j0) * D)[lane] =
+        ss::pack_bf16_rne_f64(s0 * (1.0 / BLK), s1 * (1.0 / BLK));
+}
+
+template <bool STREAM>
+void launch_metadata(int meta_kind, int blk, dim3 gr, dim3 bl, hipStream_t s, const uint8_t *kv,
+                     const int64_t *unit_off, const int32_t *nblk, int Hkv, int nblk_max, int64_t waves, int inner,
+                     int64_t bs, int64_t rs, uint16_t *m)
+{
+    if (meta_kind == SS_META_CUBOID) {
+        switch (blk) {
+        case 8: ss::launch(meta_kernel<8, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        case 16: ss::launch(meta_kernel<16, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        default: ss::launch(meta_kernel<32, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        }
+    } else {
+        switch (blk) {
+        case 8: ss::launch(meta_mean_kernel<8, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        case 16: ss::launch(meta_mean_kernel<16, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        default: ss::launch(meta_mean_kernel<32, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
+        }
+    }
 }
 
 }  // namespace
@@ -168,34 +237,23 @@ extern "C" ss_status ss_build_metadata_strided(const void *kv_base, const int64_
     SS_CHECK_ARG(block_stride > 0 && row_stride > 0 && block_stride % 16 == 0 && row_stride % 16 == 0,
                  "ss_build_metadata: strides %lld, %lld must be positive multiples of 16", (long long)block_stride,
                  (long long)row_stride);
-    const int64_t total = (int64_t)B * Hkv * nblk_max;
-    if (total == 0) return SS_OK;
+    if ((int64_t)B * nblk_max == 0) return SS_OK;
     SS_CHECK_ARG(kv_base && unit_off && nblk && meta, "ss_build_metadata: null pointer");
     SS_CHECK_ARG(((uintptr_t)kv_base & 15) == 0 && ((uintptr_t)meta & 15) == 0,
                  "ss_build_metadata: kv_base and meta must be 16-byte aligned");
-    // cuboids: 4 waves of 64/blk records per workgroup; mean keys: 4 records
-    const int64_t per_wg = meta_kind == SS_META_CUBOID ? 4 * (64 / blk) : 4;
-    const int64_t grid = (total + per_wg - 1) / per_wg;
+    const int per = meta_kind == SS_META_CUBOID ? 64 / blk : 1;  // blocks per wave
+    const int64_t waves = (int64_t)B * Hkv * ((nblk_max + per - 1) / per);
+    const int64_t grid = (waves + WAVES - 1) / WAVES;
     SS_CHECK_SUPPORTED(grid <= 0x7FFFFFFF, "ss_build_metadata: too many blocks");
     hipStream_t s = ss::as_stream(stream);
     const uint8_t *kv = static_cast<const uint8_t *>(kv_base);
-    const dim3 gr((unsigned)grid), bl(256);
+    const dim3 gr((unsigned)grid), bl(WAVES * 64);
     const int64_t bs = block_stride, rs = row_stride;
-    if (meta_kind == SS_META_CUBOID) {
-        uint16_t *m = static_cast<uint16_t *>(meta);
-        switch (blk) {
-        case 8: ss::launch(meta_kernel<8>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        case 16: ss::launch(meta_kernel<16>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        default: ss::launch(meta_kernel<32>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        }
-    } else {
-        uint32_t *m = static_cast<uint32_t *>(meta);
-        switch (blk) {
-        case 8: ss::launch(meta_mean_kernel<8>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        case 16: ss::launch(meta_mean_kernel<16>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        default: ss::launch(meta_mean_kernel<32>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, total, bs, rs, m); break;
-        }
-    }
+    const bool large = (int64_t)B * Hkv * nblk_max * blk * (d * 2) > kLargeBytes;
+    const int inner = large && row_stride > d * 2;  // other heads' rows lie between a head's rows
+    uint16_t *m = static_cast<uint16_t *>(meta);
+    (large ? launch_metadata<true> : launch_metadata<false>)(meta_kind, blk, gr, bl, s, kv, unit_off, nblk, Hkv,
+                                                             nblk_max, waves, inner, bs, rs, m);
     return ss::check_launch("ss_build_metadata");
 }
 

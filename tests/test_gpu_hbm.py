@@ -450,3 +450,51 @@ def test_llama3_8b_shape_full_size(ss, oracle_impl):
     worst2 = float(np.abs(out2 - ref).max())
     print(f"[gpu] {cfg.name}: tie-band units {len(diff)}, attention err {worst:.2e} / {worst2:.2e}")
     assert worst <= gu.ATTN_TOL and worst2 <= gu.ATTN_TOL
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("blk,Hkv,tokens,token_major", [(8, 3, 1003, True), (16, 2, 37, False), (32, 1, 999, True),
+                                                        (8, 8, 90011, False), (16, 8, 90011, True),
+                                                        (32, 8, 90011, True), (16, 8, 90011, False)])
+def test_metadata_launch_shapes(ss, kind, blk, Hkv, tokens, token_major):
+    """Metadata of two sequences, one a few blocks short of the other, from
+    token-major KV and from block records, with fewer keys than kLargeBytes
+    and with more (90011 tokens of 8 heads, both sequences: 352 MiB); block
+    counts that end inside a wave's group.  Bit-exact against min/max over
+    totalOrder keys and the fp64 mean rounded once, computed here; rows past
+    a sequence's count keep what they held."""
+    d, B = 128, 2
+    n = tokens // blk
+    nblk = torch.tensor([n, n - min(n - 1, 5)], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(tokens * 64 + blk)
+    shape = (B, n * blk, Hkv, 2, d) if token_major else (B, Hkv, n, 2, blk, d)
+    kv = torch.randn(shape, generator=g, device="cuda").bfloat16()
+    kv.view(-1)[::97] = -0.0
+    kv.view(-1)[::89] = 0.0
+    rec = blk * 2 * d * 2
+    if token_major:
+        row, step = Hkv * 2 * d * 2, blk * Hkv * 2 * d * 2
+        off = [b * n * step + h * 2 * d * 2 for b in range(B) for h in range(Hkv)]
+        keys = kv[:, :, :, 0].unflatten(1, (n, blk)).permute(0, 3, 1, 2, 4)
+    else:
+        row, step = d * 2, rec
+        off = [(b * Hkv + h) * n * rec for b in range(B) for h in range(Hkv)]
+        keys = kv[:, :, :, 0]
+    off = torch.tensor(off, dtype=torch.int64, device="cuda")
+    meta = torch.full((B, Hkv, n) + ((2, d) if kind == 0 else (d,)), 0x7ABC, dtype=torch.int16, device="cuda")
+    print(f"[gpu] metadata kind {kind}, blk {blk}, {Hkv} heads, {tokens} tokens, token-major {token_major}", flush=True)
+    ss.ss_build_metadata_strided(kv, off, nblk, B, Hkv, n, blk, d, step, row, kind, meta)
+    for b in range(B):
+        m = int(nblk[b])
+        k = keys[b, :, :m].contiguous()
+        if kind == 0:
+            bits = k.view(torch.int16)
+            order = torch.where(bits < 0, bits ^ 0x7FFF, bits)  # totalOrder as signed integers
+            lo, hi = order.amin(2), order.amax(2)
+            want = torch.stack([torch.where(x < 0, x ^ 0x7FFF, x) for x in (lo, hi)], 2)
+        else:
+            x = (k.double().sum(2) / blk).view(torch.int64)  # to 8 significant bits, ties to even
+            x = ((x + ((1 << 44) - 1) + ((x >> 45) & 1)) >> 45) << 45
+            want = x.view(torch.float64).bfloat16().view(torch.int16)
+        assert torch.equal(meta[b, :, :m], want)
+        assert bool((meta[b, :, m:] == 0x7ABC).all())
