@@ -1,39 +1,132 @@
 // Top-k block selection per (sequence, KV head) (Section 2.2), ties to the
 // lower block index, output in ascending block order.
 //
-// One workgroup per unit.  Thread t owns the R consecutive scores
-// [t*R, t*R+R) in registers as 32-bit keys whose unsigned order is the
-// float order (-0 folded onto +0; padding gets key 0, below every float).
-// The row is read with coalesced loads (each wave instruction 256
-// consecutive bytes) and handed to its owners through LDS; the loads are
-// issued before the unit's block count arrives (the row holds nblk_max
-// scores, so every load is in bounds).  A radix select finds the m-th
-// largest key (m = min(k, n)) 8 bits at a time, starting below the bits
-// shared by the smallest and largest key.  The first pass counts every key,
-// and its digits are often a handful of values (the sign and exponent bits
-// of similar scores); LDS atomics from one wave instruction to the same
-// address are processed one lane at a time, so that pass counts into 16
-// interleaved copies of the histogram (lane l adds to copy l mod 16; the
-// copies of a bin are adjacent words, so the lanes spread over banks too)
-// and sums them afterwards.  The select stops as soon as the bucket it
-// lands in is needed whole.  The selection is then {key above the bucket}
-// plus the first (m - #{above}) keys in the bucket in index order; because
-// threads own consecutive indices, one block-wide exclusive scan of two
-// counts gives every thread its output positions in ascending block order.
-// On MI355X this took the kernel from 26.2 to 14.2 us for 512 units of
-// 8192 blocks (k = 128), from 15.7 to 10.3 us for 16 units and from 27.1
-// to 15.2 us for 192 units of 16384 blocks.
+// One workgroup per unit, the unit's scores in registers as 32-bit keys whose
+// unsigned order is the float order (-0 folded onto +0; key 0, below every
+// score, for padding).  Wave w owns R*64 consecutive scores, lane l of it the
+// scores i*64 + l of those: the loads are coalesced, are issued before the
+// unit's block count arrives (the row holds nblk_max scores, so every load is
+// in bounds), and ranks in block order are ballots.
+//
+// The selection is every key above a bound and the first `quota` keys equal
+// to it.  To find the bound (m = min(k, n) keys wanted):
+//   - one wave: bit by bit from the highest
+//     bit in which the keys differ, counting the keys at or above the trial
+//     value with ballots, until exactly the wanted number is;
+//   - several waves: the range of the keys is cut into 256 equal intervals
+//     (a shift of key - lowest key) and counted into them in LDS; the interval
+//     of the m-th largest key holds few of them (about ten of 8192 Gaussian
+//     scores with k = 128).  They are collected in LDS, and every wave finds
+//     the bound among them by itself, bit by bit.  An interval with too many
+//     keys is cut again.
+// LDS atomics of one instruction to one address are done one lane at a time,
+// so the counts go to 8 copies (lane l to copy l mod 8), laid out so that the
+// copies of an interval lie in different banks and four intervals of a copy
+// are one 16-byte read (16 copies: up to 4% slower on Gaussian scores).
+//
+// What bounds it is latency: the chain of loads, exchanges between the waves
+// (LDS and a barrier) and the kernel's own launch.  Reductions and scans
+// within a wave are DPP and lane swaps, not LDS shuffles, and the loops over
+// a lane's keys are free of branches (a taken branch per key was a quarter of
+// the kernel).  Dispatch events, us, Gaussian scores, with the 8-bit radix
+// passes over consecutive scores handed out through LDS, shuffle reductions
+// and scans that this replaces, and now (an empty kernel reads about 4):
+// 8 units of 8192 blocks 9.4, 5.7; 512 units 12.1, 7.9; 256 of 2048 6.0, 4.4;
+// 192 of 16384 (k = 512) 13.0, 10.6; 8 of 65536 55.8, 21.7.  Outliers above a
+// tight band, 512 units of 8192: 19.9, 12.6; one value but for one: 52.5,
+// 14.4; 200 distinct values, 256 of 2048: 6.6, 7.7.
+#include <climits>
+
 #include "internal.hpp"
 
 namespace {
 
-constexpr int kCopies = 16;  // histogram copies of the first radix pass
+constexpr int kCopies = 8;            // copies of the interval counts
+constexpr int kPitch = 256 + 4;        // words per copy: one interval's copies lie in different banks
+constexpr int kCandRegs = 8;           // keys per lane of the last search
+constexpr int kCand = 64 * kCandRegs;  // most keys it takes
+constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gfx9 (32-bit data)
 
-__device__ __forceinline__ uint32_t score_key(float f)
+// order-preserving key of a score's bits; at least 1 (0 is padding)
+__device__ __forceinline__ uint32_t score_key(uint32_t x)
 {
-    uint32_t b = __float_as_uint(f);
-    if ((b & 0x7FFFFFFFu) == 0) b = 0;  // -0 == +0
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+    const uint32_t b = __float_as_uint(__uint_as_float(x) + 0.0f);  // -0 -> +0
+    return max(b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u), 1u);
+}
+
+// a value that is the same in every lane, as a scalar
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// minimum over the wave, in every lane
+__device__ __forceinline__ uint32_t wave_min(uint32_t x)
+{
+    x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false));   // lane ^ 1
+    x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, false));   // lane ^ 2
+    x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, false));  // mirrored in 8 lanes
+    x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x140, 0xF, 0xF, false));  // mirrored in 16 lanes
+    const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = min(h[0], h[1]);
+    const auto w = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return min(w[0], w[1]);
+}
+
+// inclusive prefix sum over the wave
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // from 1, 2, 4, 8 lanes below in the row
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // the row below's total, rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // the lower half's total, rows 2 and 3
+    return x;
+}
+
+// bits of R keys
+template <int R>
+struct bits_of {
+    typedef uint32_t type;
+};
+template <>
+struct bits_of<64> {
+    typedef unsigned long long type;
+};
+__device__ __forceinline__ int popcount(uint32_t x) { return __popc(x); }
+__device__ __forceinline__ int popcount(unsigned long long x) { return __popcll(x); }
+__device__ __forceinline__ int lowest(uint32_t x) { return __ffs(x) - 1; }
+__device__ __forceinline__ int lowest(unsigned long long x) { return __ffsll(x) - 1; }
+
+// The selection: keys above `above`, and the first `quota` keys equal to it.
+struct bound_t {
+    uint32_t above;
+    int quota;
+};
+
+// The bound of the `want` largest of the wave's keys lo + off[*] (offsets of
+// 0, padding among them, only win if nothing else is left), 0 < want <= the
+// keys there.  span: no offset is larger.
+template <int N>
+__device__ __forceinline__ bound_t search(const uint32_t (&off)[N], uint32_t lo, uint32_t span, int want)
+{
+    uint32_t t = 0;
+    int at_least = INT_MAX;  // keys at or above t: the whole set at t = 0
+    for (int bit = span ? 31 - __clz(span) : -1; bit >= 0; --bit) {
+        const uint32_t trial = t | 1u << bit;
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) c += __popcll(__ballot(off[i] >= trial));
+        if (c >= want) {
+            t = trial;
+            at_least = c;
+            if (c == want) break;
+        }
+    }
+    if (at_least == want) return {lo + t - 1, 0};
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) c += __popcll(__ballot(off[i] > t));
+    return {lo + t, want - c};
 }
 
 template <int NT, int R>
@@ -42,228 +135,218 @@ __global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scor
                                                   int32_t *__restrict__ mirror)
 {
     constexpr int NW = NT / 64;
-    constexpr bool kStaged = NT * R <= 16384;  // the row staged through LDS (up to 64 KiB)
-    static_assert(R % 4 == 0 && (R & (R - 1)) == 0, "R: a power of two, at least 4");
-    __shared__ __align__(16) int stage[kStaged ? NT * R : 4];
-    __shared__ __align__(16) int rep[256 * kCopies];  // the first pass's histogram copies, bin-major
-    __shared__ int hist[2][256];                       // later passes, alternating
-    __shared__ int wave_tot[2][NW];
-    __shared__ uint32_t red_min[NW], red_max[NW];
-    __shared__ int pick[2][3];
-
     const int u = blockIdx.x;
     const int b = u / Hkv;
     const float *s = scores + (int64_t)u * nblk_max;
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    const int base = t * R;
-
-    {
-        int4 *z = reinterpret_cast<int4 *>(rep);
-        for (int i = t; i < 256 * kCopies / 4; i += NT) z[i] = make_int4(0, 0, 0, 0);
-    }
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int e0 = wave * (64 * R) + lane;  // the lane's first score
 
     // the whole row's loads first; the block count masks them afterwards
+    // (buffer loads: those past nblk_max read as zero)
+    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc((void *)s, (short)0, nblk_max * 4, kBufferFlags);
     uint32_t key[R];
-    if constexpr (kStaged) {
-        // each wave instruction reads 64 consecutive scores; LDS turns them
-        // into each thread's R consecutive ones.  Float e goes to the word
-        // R*o + 4*((q + rot) mod G) + i of its owner o = e / R (q = e mod R / 4,
-        // i = e mod 4, G = R/4 chunks per thread, rot = o*G/16 mod G), so the
-        // owners' 16-byte reads of one instruction fall on distinct banks.
-        constexpr int G = R / 4;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int e = j * NT + t;
-            const uint32_t v = e < nblk_max ? __float_as_uint(s[e]) : 0u;
-            const int o = e / R, q = (e % R) >> 2;
-            stage[o * R + 4 * ((q + ((o * G) >> 4)) % G) + (e & 3)] = (int)v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const int4 v = *reinterpret_cast<const int4 *>(stage + base + 4 * ((q + ((t * G) >> 4)) % G));
-            key[4 * q + 0] = score_key(__int_as_float(v.x));
-            key[4 * q + 1] = score_key(__int_as_float(v.y));
-            key[4 * q + 2] = score_key(__int_as_float(v.z));
-            key[4 * q + 3] = score_key(__int_as_float(v.w));
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) key[r] = (base + r < nblk_max) ? score_key(s[base + r]) : 0u;
-    }
-
+    for (int i = 0; i < R; ++i) key[i] = __builtin_amdgcn_raw_buffer_load_b32(row, (e0 + i * 64) * 4, 0, 0);
+    __shared__ __align__(16) int count[NW > 1 ? kCopies * kPitch : 4];
+    auto clear = [&] {
+        int4 *z = reinterpret_cast<int4 *>(count);
+        for (int i = t; i < kCopies * kPitch / 4; i += NT) z[i] = make_int4(0, 0, 0, 0);
+    };
+    if constexpr (NW > 1) clear();
     int n = nblk[b];
     n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
     const int m = k < n ? k : n;
     int32_t *out = sel + (int64_t)u * k;
     int32_t *out2 = mirror ? mirror + (int64_t)u * k : nullptr;  // copy in mapped host memory
-
     for (int i = m + t; i < k; i += NT) {
         out[i] = -1;
         if (out2) out2[i] = -1;
     }
     if (m == 0) return;
-    auto valid = [&](int r) { return base + r < n; };
 #pragma unroll
-    for (int r = 0; r < R; ++r) key[r] = valid(r) ? key[r] : 0u;
+    for (int i = 0; i < R; ++i) key[i] = e0 + i * 64 < n ? score_key(key[i]) : 0u;
 
-    // smallest and largest valid key
-    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+    bound_t bound = {0u, 0};  // every key, where all are selected
+    if (m < n) {
+        // smallest and largest key (padding wraps to the largest)
+        uint32_t lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu;  // hi: complement
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (valid(r)) {
-            kmin = min(kmin, key[r]);
-            kmax = max(kmax, key[r]);
+        for (int i = 0; i < R; ++i) {
+            lo = min(lo, key[i] - 1u);
+            hi = min(hi, ~key[i]);
         }
+        lo = wave_min(lo);
+        hi = wave_min(hi);
+        if constexpr (NW == 1) {
+            lo = uniform(lo) + 1u;
+            uint32_t off[R];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    }
-    if (lane == 0) {
-        red_min[wave] = kmin;
-        red_max[wave] = kmax;
-    }
-    __syncthreads();
-    kmin = red_min[0];
-    kmax = red_max[0];
+            for (int i = 0; i < R; ++i) off[i] = key[i] ? key[i] - lo : 0u;
+            bound = search(off, lo, ~uniform(hi) - lo, m);
+        } else {
+            __shared__ uint32_t cand[kCand];
+            __shared__ uint32_t red_lo[NW], red_hi[NW];
+            __shared__ int pick[3], n_cand;
+            if (lane == 0) {
+                red_lo[wave] = lo;
+                red_hi[wave] = hi;
+            }
+            if (t == 0) n_cand = 0;
+            __syncthreads();
 #pragma unroll
-    for (int w = 1; w < NW; ++w) {
-        kmin = min(kmin, red_min[w]);
-        kmax = max(kmax, red_max[w]);
-    }
-
-    // Radix select below the shared prefix.  Afterwards the keys with
-    // (key & pmask) == prefix form the bucket that holds the m-th largest key,
-    // and krem of them are selected.  Pass p counts into hist[p & 1] (the
-    // first into the copies, summed into hist[0]); while wave 0 scans it, the
-    // other waves clear the other buffer for the next pass, so a pass takes
-    // two barriers.
-    uint32_t prefix = kmin, pmask = 0xFFFFFFFFu;
-    int krem = m;
-    if (kmin != kmax) {
-        const int top = 31 - __clz(kmin ^ kmax);  // highest differing bit
-        pmask = top == 31 ? 0u : ~((2u << top) - 1u);  // bits above it are shared
-        prefix = kmax & pmask;
-        for (int hi_bit = top, p = 0;; hi_bit -= 8, ++p) {
-            const int lo_bit = hi_bit >= 7 ? hi_bit - 7 : 0;
-            const int width = hi_bit - lo_bit + 1;
-            const uint32_t dmask = (1u << width) - 1u;
-            const int cur = p & 1;
-            if (p == 0) {
-                // every valid key shares the prefix: no test
-                const int c = lane & (kCopies - 1);
+            for (int w = 0; w < NW; ++w) {
+                lo = min(lo, red_lo[w]);
+                hi = min(hi, red_hi[w]);
+            }
+            lo = uniform(lo) + 1u;
+            const uint32_t top = ~uniform(hi);
+            uint32_t span = top - lo;  // the bound lies in [lo, lo + span]
+            int want = m;              // keys wanted from there
+            for (;;) {
+                if (span == 0) {
+                    bound = {lo, want};
+                    break;
+                }
+                const int bits = 32 - __clz(span);
+                const int shift = bits > 8 ? bits - 8 : 0;
+                const int c = (lane & (kCopies - 1)) * kPitch;
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (valid(r)) atomicAdd(&rep[((key[r] >> lo_bit) & dmask) * kCopies + c], 1);
+                for (int i = 0; i < R; ++i)
+                    if (key[i] - lo <= span) atomicAdd(&count[c + ((key[i] - lo) >> shift)], 1);
                 __syncthreads();
-                for (int i = t; i < 256; i += NT) {
-                    const int4 *row = reinterpret_cast<const int4 *>(rep + i * kCopies);
-                    int sum = 0;
+                if (wave == 0) {
+                    // lane l holds intervals 255-4l .. 252-4l (descending order)
+                    int4 v = make_int4(0, 0, 0, 0);
 #pragma unroll
-                    for (int j = 0; j < kCopies / 4; ++j) {
-                        const int4 v = row[j];
-                        sum += v.x + v.y + v.z + v.w;
+                    for (int i = 0; i < kCopies; ++i) {
+                        const int4 y = *reinterpret_cast<const int4 *>(count + i * kPitch + 252 - 4 * lane);
+                        v.x += y.x;
+                        v.y += y.y;
+                        v.z += y.z;
+                        v.w += y.w;
                     }
-                    hist[0][i] = sum;
-                }
-            } else {
+                    const int sum = (v.x + v.y) + (v.z + v.w);
+                    const int incl = wave_scan(sum);
+                    const int above = incl - sum;  // keys in higher intervals than this lane's
+                    if (above < want && want <= incl) {
+                        const int in[4] = {v.w, v.z, v.y, v.x};
+                        int acc = above;
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (valid(r) && (key[r] & pmask) == prefix)
-                        atomicAdd(&hist[cur][(key[r] >> lo_bit) & dmask], 1);
-            }
-            __syncthreads();
-            if (wave == 0) {
-                // lane l holds digits 255-4l .. 252-4l (descending order)
-                int c[4], sum = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    c[i] = hist[cur][255 - 4 * lane - i];
-                    sum += c[i];
-                }
-                int incl = sum;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    int y = __shfl_up(incl, o);
-                    if (lane >= o) incl += y;
-                }
-                int above = incl - sum;  // keys in higher digits than this lane's
-                // the digit where the krem-th largest falls
-                if (above < krem && krem <= incl) {
-                    int acc = above;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (acc < krem && krem <= acc + c[i]) {
-                            pick[cur][0] = 255 - 4 * lane - i;
-                            pick[cur][1] = krem - acc;
-                            pick[cur][2] = c[i];
+                        for (int i = 0; i < 4; ++i) {
+                            if (acc < want && want <= acc + in[i]) {
+                                pick[0] = 255 - 4 * lane - i;
+                                pick[1] = want - acc;
+                                pick[2] = in[i];
+                            }
+                            acc += in[i];
                         }
-                        acc += c[i];
                     }
                 }
-            } else {
-                for (int i = t - 64; i < 256; i += NT - 64) hist[cur ^ 1][i] = 0;
+                __syncthreads();
+                lo += uniform((uint32_t)pick[0]) << shift;
+                span = min((1u << shift) - 1u, top - lo);  // an interval past `top` could wrap to the padding
+                want = uniform(pick[1]);
+                const int held = uniform(pick[2]);
+                if (want == held) {  // the whole interval
+                    bound = {lo - 1u, 0};
+                    break;
+                }
+                if (span && held <= kCand) {
+#pragma unroll
+                    for (int h = 0; h < R; h += 32) {
+                        // per lane the bits of its keys there; branches only for the few waves that have any
+                        uint32_t bits = 0;
+#pragma unroll
+                        for (int i = h; i < R && i < h + 32; ++i) bits |= (key[i] - lo <= span ? 1u : 0u) << (i - h);
+                        if (!__ballot(bits != 0)) continue;
+                        const int incl = wave_scan(__popc(bits));
+                        int at = 0;
+                        if (lane == 63) at = atomicAdd(&n_cand, incl);
+                        at = __builtin_amdgcn_readlane(at, 63) + incl - __popc(bits);
+                        while (__ballot(bits != 0)) {
+                            const int low = __ffs(bits) - 1;
+                            uint32_t v = 0;
+#pragma unroll
+                            for (int i = h; i < R && i < h + 32; ++i) v = low == i - h ? key[i] : v;
+                            if (bits) cand[at] = v - lo;
+                            ++at;
+                            bits &= bits - 1;
+                        }
+                    }
+                    __syncthreads();
+                    if (held <= 64) {
+                        const uint32_t off[1] = {lane < held ? cand[lane] : 0u};
+                        bound = search(off, lo, span, want);
+                    } else {
+                        uint32_t off[kCandRegs];
+#pragma unroll
+                        for (int i = 0; i < kCandRegs; ++i) off[i] = i * 64 + lane < held ? cand[i * 64 + lane] : 0u;
+                        bound = search(off, lo, span, want);
+                    }
+                    break;
+                }
+                if (span) {
+                    clear();
+                    __syncthreads();
+                }
             }
-            __syncthreads();
-            const uint32_t digit = (uint32_t)pick[cur][0];
-            krem = pick[cur][1];
-            const int in_bucket = pick[cur][2];
-            prefix |= digit << lo_bit;
-            pmask |= dmask << lo_bit;
-            if (krem == in_bucket || lo_bit == 0) break;  // the whole bucket is selected, or single keys
         }
     }
 
-    // Output positions in block order: with gt_before and eq_before the counts
-    // of keys above the bucket and in it over the threads before this one, the
-    // bucket's first krem keys are taken in order, so this thread takes
-    // min(n_eq, krem - eq_before) of its bucket keys and its first output goes
-    // to gt_before + min(krem, eq_before).
-    int n_gt = 0, n_eq = 0;
+    // Output positions in block order.  The lanes hand the selected scores'
+    // bits to the lane that owns R consecutive ones (all of them this wave's
+    // own, so the waves exchange only their totals); a scan of the lanes' bit
+    // counts places each lane's first output.  A key equal to the bound is
+    // taken if fewer than `quota` of them come before it.
+    typedef typename bits_of<R>::type bits_t;
+    __shared__ unsigned long long map[2][NW][R];
+    __shared__ int tot[2][NW];
+    auto hand_over = [&](int which, auto taken) -> bits_t {
+        uint32_t lo = 0, hi = 0;
+        int c = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t kk = key[r] & pmask;
-        n_gt += (valid(r) && kk > prefix) ? 1 : 0;
-        n_eq += (valid(r) && kk == prefix) ? 1 : 0;
-    }
-    int x_gt = n_gt, x_eq = n_eq;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y_gt = __shfl_up(x_gt, o), y_eq = __shfl_up(x_eq, o);
-        if (lane >= o) {
-            x_gt += y_gt;
-            x_eq += y_eq;
+        for (int i = 0; i < R; ++i) {
+            const unsigned long long mask = __ballot(taken(key[i]));
+            lo = lane == i ? (uint32_t)mask : lo;
+            hi = lane == i ? (uint32_t)(mask >> 32) : hi;
+            c += __popcll(mask);
         }
-    }
-    if (lane == 63) {
-        wave_tot[0][wave] = x_gt;
-        wave_tot[1][wave] = x_eq;
-    }
-    __syncthreads();
-    int gt_before = x_gt - n_gt, eq_before = x_eq - n_eq;
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-        if (w < wave) {
-            gt_before += wave_tot[0][w];
-            eq_before += wave_tot[1][w];
+        if (lane < R) map[which][wave][lane] = (unsigned long long)hi << 32 | lo;
+        if (lane == 0) tot[which][wave] = c;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (R == 64) {
+            return map[which][wave][lane];
+        } else {
+            const uint32_t w = reinterpret_cast<const uint32_t *>(map[which][wave])[lane * R / 32];
+            return (w >> (lane * R % 32)) & ((1u << R) - 1u);
         }
-    int eq_quota = krem - eq_before;
-    eq_quota = eq_quota < 0 ? 0 : (eq_quota > n_eq ? n_eq : eq_quota);
-    int pos = gt_before + (eq_before < krem ? eq_before : krem);
+    };
+    bits_t bits = hand_over(0, [&](uint32_t x) { return x > bound.above; }), eq_bits = 0;
+    if (bound.quota) eq_bits = hand_over(1, [&](uint32_t x) { return x == bound.above; });
+    int pos = wave_scan(popcount(bits)) - popcount(bits);
+    if constexpr (NW > 1) {
+        __syncthreads();
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t kk = key[r] & pmask;
-        const bool eq = valid(r) && kk == prefix;
-        const bool take = (valid(r) && kk > prefix) || (eq && eq_quota > 0);
-        if (eq && eq_quota > 0) --eq_quota;
-        if (take && pos < m) {  // pos < m always holds; the guard keeps writes in range
-            out[pos] = base + r;
-            if (out2) out2[pos] = base + r;
-            ++pos;
-        }
+        for (int w = 0; w < NW; ++w) pos += w < wave ? tot[0][w] : 0;
     }
+    if (bound.quota) {
+        int before = wave_scan(popcount(eq_bits)) - popcount(eq_bits);
+        if constexpr (NW > 1) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) before += w < wave ? tot[1][w] : 0;
+        }
+        pos += min(before, bound.quota);
+        int left = max(bound.quota - before, 0);
+        for (bits_t e = eq_bits; e && left > 0; e &= e - 1, --left) bits |= e & (~e + 1);
+    }
+    const int first = (wave * 64 + lane) * R;
+    for (; bits; bits &= bits - 1, ++pos)
+        if (pos < m) {  // always holds; the guard keeps writes in range
+            const int j = first + lowest(bits);
+            out[pos] = j;
+            if (out2) out2[pos] = j;
+        }
 }
 
 template <int NT, int R>
@@ -283,12 +366,15 @@ ss_status launch_topk(const float *scores, const int32_t *nblk, int B, int Hkv, 
 {
     const int units = B * Hkv;
     if (units == 0) return SS_OK;
-    // Workgroup width per size class: 512 threads from 2048 blocks up, so that
-    // each thread holds at most 16 keys.  On MI355X (k = 128) this took a
-    // 16-unit launch over 8192 blocks from 14.2 to 11.0 us and the 512-unit
-    // one from 26.3 to 18.0 us against 256 threads of 32 keys, and 1024
-    // threads of 8 keys measured 11.4 and 22.9 us.
-    if (nblk_max <= 256 * 4) launch_variant<256, 4>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
+    // Threads x scores per thread.  A wave alone finds the bound without an
+    // exchange, but pays for every key in every bit: it is level with 256
+    // threads up to 256 blocks (4.1 us) and slower beyond (512: 4.4 against
+    // 4.2; 1024: 5.5 against 4.1).  From 2048 blocks, 512 threads of 4 to 16
+    // keys against 1024 of half as many: 4.5 and 5.6 us for 256 units of 2048
+    // blocks, 6.1 and 8.0 for 512 of 4096, 8.0 and 9.6 for 512 of 8192.
+    if (nblk_max <= 64 * 4) launch_variant<64, 4>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
+    else if (nblk_max <= 256 * 2) launch_variant<256, 2>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
+    else if (nblk_max <= 256 * 4) launch_variant<256, 4>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
     else if (nblk_max <= 512 * 4) launch_variant<512, 4>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
     else if (nblk_max <= 512 * 8) launch_variant<512, 8>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);
     else if (nblk_max <= 512 * 16) launch_variant<512, 16>(scores, nblk, units, Hkv, nblk_max, k, sel, mirror, s);

@@ -498,3 +498,33 @@ def test_metadata_launch_shapes(ss, kind, blk, Hkv, tokens, token_major):
             want = x.view(torch.float64).bfloat16().view(torch.int16)
         assert torch.equal(meta[b, :, :m], want)
         assert bool((meta[b, :, m:] == 0x7ABC).all())
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 256, 257, 512, 513, 1024, 1025, 2049, 4097, 8193, 16385, 65536])
+def test_topk_launch_shapes_and_extremes(ss, oracle_impl, n):
+    """Either side of the launch shapes' row lengths, rows one score short of
+    the row's room among them; rows of the largest and smallest floats with
+    infinities (so that the keys span all 32 bits), of subnormals, of one
+    value, of neighbouring floats, of outliers above a tight band, and one
+    with more equal scores at its bound than the last search takes; every k
+    from one block to all of them.  Equal to the oracle's selection."""
+    rng = np.random.default_rng(n)
+    near = np.arange(n, dtype=np.uint32)
+    rng.shuffle(near)
+    rows = np.stack([
+        np.where(rng.random(n) < 0.5, np.float32(-np.inf), np.finfo(np.float32).max * rng.uniform(-1, 1, n)),
+        np.where(rng.random(n) < 0.01, np.float32(np.inf), np.float32(-np.inf)),
+        rng.integers(-50, 50, n) * np.float32(1e-45),
+        np.full(n, np.float32(-3.0)),
+        (np.float32(246).view(np.uint32) + near).view(np.float32),
+        np.where(np.arange(n) % 97 == 5, np.float32(5e4), np.float32(30)) + 1e-3 * rng.standard_normal(n),
+        np.where(rng.random(n) < 0.9, np.float32(1), rng.standard_normal(n)),
+        246 + 21 * rng.standard_normal(n)]).astype(np.float32)
+    B, Hkv = 4, 2
+    sc = rows.reshape(B, Hkv, n)
+    nblk = np.array([n, max(n - 1, 0), n, n // 2], np.int32)
+    for k in sorted({1, max(n // 3, 1), max(n - 1, 1), n, n + 3, min(n, 128)}):
+        sel = torch.empty(B, Hkv, k, dtype=torch.int32, device="cuda")
+        ss.ss_select_topk(torch.from_numpy(sc).cuda(), torch.from_numpy(nblk).cuda(), B, Hkv, n, k, sel)
+        ref = oracle_impl.select(sc.astype(np.float64), nblk, k)
+        np.testing.assert_array_equal(sel.cpu().numpy(), ref, err_msg=f"n={n} k={k}")
