@@ -30,11 +30,12 @@
 // P enters the PV product as a bf16 hi + lo pair, which keeps about 16
 // significant bits of every probability.
 //
-// Work split: grid (unit, split); a workgroup of 4 waves owns a contiguous
-// range of 16-token steps, waves take steps round-robin, the 4 wave partials
-// are merged in LDS in wave order, and with several splits a second kernel
-// merges the split partials in split order.  All merges run in a fixed
-// order, so results do not depend on scheduling.
+// Work split: grid (unit, split); a workgroup of 4 or 8 waves owns a
+// contiguous range of 16-token steps, waves take steps round-robin, the wave
+// partials are merged in LDS in wave order (a wave's partial output takes the
+// place of its K tile), and with several splits a second kernel merges the
+// split partials in split order.  All merges run in a fixed order, so results
+// do not depend on scheduling.  plan() says how waves and splits are chosen.
 #include <mutex>
 #include <unordered_map>
 
@@ -43,8 +44,8 @@
 namespace {
 
 constexpr int D = ss::kHeadDim;
-constexpr int WAVES = 4;
 constexpr int TOK = 16;  // tokens per wave step
+constexpr int CUS = 256;
 constexpr int KPITCH = D * 2 / 16 + 1;  // LDS row pitch of a staged K tile, in 16-byte units
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -75,11 +76,11 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 struct split_plan {
-    int splits, steps_per_split;
+    int waves, splits, steps_per_split;
 };
 
-template <int BLK>
-__global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict__ q, const uint8_t *__restrict__ kv,
+template <int BLK, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : WAVES / 4) void attn_kernel(const uint16_t *__restrict__ q, const uint8_t *__restrict__ kv,
                                                       const int64_t *__restrict__ region_off,
                                                       const int32_t *__restrict__ slots,
                                                       const int32_t *__restrict__ capacity, int slot_limit, int Hq,
@@ -88,8 +89,9 @@ __global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict
 {
     constexpr int64_t REC = 2LL * BLK * D * 2;
     __shared__ float sm_m[WAVES][16], sm_l[WAVES][16];
-    __shared__ float sm_o[WAVES][16][D + 4];
-    __shared__ uint4 kst[WAVES][TOK * KPITCH];  // each wave's K tile of the current step
+    // per wave: the K tile of its current step, then its partial output [16][D + 4]
+    __shared__ __align__(16) unsigned char sm_wave[WAVES][16 * (D + 4) * 4];
+    static_assert(TOK * KPITCH * 16 <= 16 * (D + 4) * 4, "the K tile fits the partial output's place");
 
     const int u = blockIdx.x, split = blockIdx.y, splits = gridDim.y;
     const int b = u / Hkv, g = u - b * Hkv;
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict
         // K rows through the wave's LDS tile into A fragments: row `col`,
         // channels m*32 + 8L .. +7 (the padded pitch keeps each 16-lane group
         // of a fragment read on 64 distinct banks)
-        uint4 *kt = kst[wave];
+        uint4 *kt = reinterpret_cast<uint4 *>(sm_wave[wave]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) kt[(4 * i + L) * KPITCH + col] = x.kr[i];
         f32x4_t sacc = {0.f, 0.f, 0.f, 0.f};
@@ -236,10 +238,11 @@ __global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict
         sm_m[wave][col] = mrun;
         sm_l[wave][col] = lrun;
     }
+    if (col < G) {
+        float *o_row = reinterpret_cast<float *>(sm_wave[wave]) + col * (D + 4);
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sm_o[wave][col][16 * t + L * 4 + i] = o[t][i];
+        for (int t = 0; t < 8; ++t) *reinterpret_cast<f32x4_t *>(o_row + 16 * t + L * 4) = o[t];
+    }
     __syncthreads();
 
     for (int idx = threadIdx.x; idx < G * D; idx += blockDim.x) {
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict
             for (int w = 0; w < WAVES; ++w) {
                 const float sc = __builtin_amdgcn_exp2f(sm_m[w][h] - M);
                 lsum += sc * sm_l[w][h];
-                osum += sc * sm_o[w][h][ch];
+                osum += sc * reinterpret_cast<const float *>(sm_wave[w])[h * (D + 4) + ch];
             }
         }
         if (splits == 1) {
@@ -269,38 +272,114 @@ __global__ __launch_bounds__(256, 3) void attn_kernel(const uint16_t *__restrict
     }
 }
 
-__global__ __launch_bounds__(D) void combine_kernel(const float *__restrict__ ws, int Hq, int Hkv, int G, int splits,
-                                                    float *__restrict__ out)
+// two floats, aligned as one is (the workspace is the caller's)
+typedef float f32x2_t __attribute__((ext_vector_type(2), aligned(4)));
+
+// maximum over the wave, in every lane
+__device__ __forceinline__ float wave_max(float x)
 {
-    const int u = blockIdx.x, h = blockIdx.y, ch = threadIdx.x;
+    auto step = [](float v, int y) { return fmaxf(v, __int_as_float(y)); };
+    x = step(x, __builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));   // lane ^ 1
+    x = step(x, __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));   // lane ^ 2
+    x = step(x, __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false));  // mirrored in 8 lanes
+    x = step(x, __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, false));  // mirrored in 16 lanes
+    const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+
+// One wave per (unit, head), two channels per lane.  The splits' maxima and
+// sums are read side by side, one split per lane, together with the first
+// partials (none of the loads waits for another), and the weights go round as
+// scalars.  Latency bounds it: 8 splits of 32 heads took 3.3 us with each
+// thread walking the splits twice, 2.5 now; 12 splits of 308 heads 6.4 and 4.6
+// (of which about 2 are the launch).
+__global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ ws, int Hq, int Hkv, int G, int splits,
+                                                     float *__restrict__ out)
+{
+    constexpr int CHUNK = 16;
+    const int u = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
     const int b = u / Hkv, g = u - b * Hkv;
     const float *p = ws + ((int64_t)u * splits * G + h) * (D + 2);
     const int64_t stride = (int64_t)G * (D + 2);
-    float M = -INFINITY;
-    for (int s = 0; s < splits; ++s) M = fmaxf(M, p[s * stride]);
-    float lsum = 0.f, osum = 0.f;
+    f32x2_t x[CHUNK];
+    auto load = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < CHUNK; ++i)
+            x[i] = *reinterpret_cast<const f32x2_t *>(p + min(s0 + i, splits - 1) * stride + 2 + 2 * lane);
+    };
+    f32x2_t ml = {-INFINITY, 0.f};
+    if (lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + lane * stride);
+    load(0);
+    float M = ml.x;
+    for (int s = lane + 64; s < splits; s += 64) M = fmaxf(M, p[s * stride]);
+    M = wave_max(M);
+    float lsum = 0.f;
+    f32x2_t osum = {0.f, 0.f};
     if (M != -INFINITY)
-        for (int s = 0; s < splits; ++s) {
-            const float *ps = p + s * stride;
-            const float sc = __builtin_amdgcn_exp2f(ps[0] - M);
-            lsum += sc * ps[1];
-            osum += sc * ps[2 + ch];
+        for (int s0 = 0; s0 < splits; s0 += CHUNK) {
+            const int at = s0 & 63;  // lane of the chunk's first split
+            if (s0 > 0) {
+                load(s0);
+                if (at == 0) {
+                    ml = f32x2_t{-INFINITY, 0.f};
+                    if (s0 + lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + (s0 + lane) * stride);
+                }
+            }
+            const float w = __builtin_amdgcn_exp2f(ml.x - M);  // 0 past the last split
+            const float wl = w * ml.y;
+#pragma unroll
+            for (int i = 0; i < CHUNK; ++i) {
+                const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), at + i));
+                lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), at + i));
+                osum.x += sc * x[i].x;
+                osum.y += sc * x[i].y;
+            }
         }
-    out[((int64_t)b * Hq + g * G + h) * D + ch] = lsum > 0.f ? osum / lsum : 0.f;
+    f32x2_t y = {0.f, 0.f};
+    if (lsum > 0.f) y = f32x2_t{osum.x / lsum, osum.y / lsum};
+    *reinterpret_cast<f32x2_t *>(out + ((int64_t)b * Hq + g * G + h) * D + 2 * lane) = y;
 }
 
+// Waves per workgroup and splits per unit.
+//
+// One workgroup of 8 waves per unit writes the output itself, with no second
+// launch.  It is taken
+//   - below 32 steps (k * blk < 512 tokens), where splits would leave a wave
+//     one or two steps: 4 units of 16 steps 5.0 us against 5.7 with 4 waves
+//     and 7.1 with 4 splits of them; 64 of 24 steps 7.5 against 8.1 and 8.3;
+//   - up to 256 units, one per CU, where that is as fast as what the splits
+//     save: from 144 units at any length (160 units of 128 steps 29.3 us
+//     against 33.4, 192 units 32.4 against 41.6, 256 units 42.3 against 47.0),
+//     from 96 up to 96 steps (96 units of 64 steps 14.8 against 16.3, but of
+//     128 steps 25.6 against 24.0);
+//   - from 384 to 511 units, two rounds of the CUs (448 units of 128 steps
+//     71.9 us against 79.4 with two splits; 320 units 63.7 against 57.8).
+// Otherwise 4 waves, at least 4 steps a split (8 where there are more
+// workgroups than CUs), and the splits for which the fullest CU has least to
+// do: a step takes a CU about 0.32 us of the chip's bandwidth, a workgroup
+// costs about 0.012 us, the second launch 4 us (44 units of 256 steps: 5
+// splits 20.7 us, 12 splits 22.5; 264 units of 128 steps: 2 splits 56.5 us, 3
+// splits 52.8).  units * splits stays below 1024, which bounds the partials.
 split_plan plan(int units, int k, int blk)
 {
     const int steps = (int)(((int64_t)k * blk + TOK - 1) / TOK);
-    const int target_wg = 512;  // two 4-wave workgroups per CU
-    int splits = units > 0 ? (target_wg + units - 1) / units : 1;
-    int max_splits = steps / (WAVES * 4);  // keep >= 4 steps per wave
-    if (max_splits < 1) max_splits = 1;
-    if (splits > max_splits) splits = max_splits;
-    if (splits < 1) splits = 1;
-    int sps = (steps + splits - 1) / splits;
-    splits = (steps + sps - 1) / sps;
-    return {splits, sps};
+    if ((units <= 256 && (steps < 32 || units >= 144 || (units >= 96 && steps <= 96))) ||
+        (units >= 384 && units < 512 && steps >= 32))
+        return {8, 1, steps};
+    int best = 1;
+    float least = 0.f;
+    for (int n = 1; n <= 32 && (n == 1 || (units * n < 1024 && n * (units * n <= CUS ? 4 : 8) <= steps)); ++n) {
+        const float rounds = (float)((units * n + CUS - 1) / CUS);
+        const float cost = rounds / n * steps * 0.32f + (n > 1 ? 0.012f * units * n + 4.f : 0.f);
+        if (n == 1 || cost < least) {
+            best = n;
+            least = cost;
+        }
+    }
+    const int sps = (steps + best - 1) / best;
+    return {4, (steps + sps - 1) / sps, sps};
 }
 
 }  // namespace
@@ -343,22 +422,22 @@ extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, con
     const uint16_t *qq = static_cast<const uint16_t *>(q);
     const uint8_t *kv = static_cast<const uint8_t *>(kv_base);
     float *ws = static_cast<float *>(workspace);
-    switch (blk) {
-    case 8: ss::launch(attn_kernel<8>, grid, dim3(256), s, qq, kv, region_off, slots, capacity, slot_limit, Hq, Hkv, G, k, scale_log2, sp.steps_per_split, out, ws); break;
-    case 16: ss::launch(attn_kernel<16>, grid, dim3(256), s, qq, kv, region_off, slots, capacity, slot_limit, Hq, Hkv, G, k, scale_log2, sp.steps_per_split, out, ws); break;
-    default: ss::launch(attn_kernel<32>, grid, dim3(256), s, qq, kv, region_off, slots, capacity, slot_limit, Hq, Hkv, G, k, scale_log2, sp.steps_per_split, out, ws); break;
-    }
+    const bool wide = sp.waves == 8;
+    auto *kernel = wide ? attn_kernel<32, 8> : attn_kernel<32, 4>;
+    if (blk == 8) kernel = wide ? attn_kernel<8, 8> : attn_kernel<8, 4>;
+    else if (blk == 16) kernel = wide ? attn_kernel<16, 8> : attn_kernel<16, 4>;
+    ss::launch(kernel, grid, dim3(sp.waves * 64), s, qq, kv, region_off, slots, capacity, slot_limit, Hq, Hkv, G, k,
+               scale_log2, sp.steps_per_split, out, ws);
     ss_status st = ss::check_launch("ss_sparse_attention");
     if (st != SS_OK || sp.splits == 1) return st;
-    combine_kernel<<<dim3(units, G), dim3(D), 0, s>>>(ws, Hq, Hkv, G, sp.splits, out);
+    combine_kernel<<<dim3(units, G), dim3(64), 0, s>>>(ws, Hq, Hkv, G, sp.splits, out);
     return ss::check_launch("ss_sparse_attention(combine)");
 }
 
 // ------------------------------------------------- allocation-free variant
 // The split partials of ss_sparse_attention_static live in this file-scope
 // device array instead of a caller workspace.  Every supported shape fits:
-// with more than one split, units * splits < units + 512 <= 1023 and
-// G <= 16, so the partials take at most 1023 * 16 * (128 + 2) * 4 bytes.
+// with more than one split, units * splits <= 1023 and G <= 16, so the partials take at most 1023 * 16 * (128 + 2) * 4 bytes.
 // Host code never uses the array's name as an address: each device's copy
 // is looked up once with hipGetSymbolAddress and that pointer is passed on.
 namespace {

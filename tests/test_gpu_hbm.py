@@ -528,3 +528,42 @@ def test_topk_launch_shapes_and_extremes(ss, oracle_impl, n):
         ss.ss_select_topk(torch.from_numpy(sc).cuda(), torch.from_numpy(nblk).cuda(), B, Hkv, n, k, sel)
         ref = oracle_impl.select(sc.astype(np.float64), nblk, k)
         np.testing.assert_array_equal(sel.cpu().numpy(), ref, err_msg=f"n={n} k={k}")
+
+
+@pytest.mark.parametrize("units,G,blk,k", [(1, 16, 8, 1), (3, 4, 16, 15), (3, 4, 16, 31), (2, 7, 16, 32), (5, 7, 8, 65),
+                                           (1, 5, 16, 700), (95, 4, 16, 96), (96, 4, 16, 97), (96, 1, 32, 48),
+                                           (143, 4, 16, 40), (144, 4, 16, 40), (256, 2, 8, 33), (257, 2, 16, 40),
+                                           (341, 1, 16, 33), (383, 2, 16, 32), (384, 2, 16, 32), (511, 1, 16, 33),
+                                           (512, 1, 16, 33)])
+def test_attention_launch_shapes(ss, units, G, blk, k):
+    """Either side of the lines between one workgroup of 8 waves per unit,
+    one of 4 waves, and splits; entries that are not selected in between, a
+    unit with none, and steps that do not divide among waves and splits.
+    Against float64 on the GPU: products are exact and sums 32-bit, so the
+    probabilities' 16 bits bound the error, 2^-15 of the largest |V|."""
+    d, slots = 128, k + 3
+    g = torch.Generator(device="cuda").manual_seed(units * 1000 + k)
+    kv = torch.randn(units, slots, 2, blk * d, generator=g, device="cuda").bfloat16()
+    q = torch.randn(units, G, d, generator=g, device="cuda").bfloat16()
+    sel = torch.rand(units, slots, generator=g, device="cuda").topk(k, dim=1).indices.to(torch.int32)
+    sel[torch.rand(units, k, generator=g, device="cuda") < 0.1] = -1
+    sel[units // 2] = -1
+    cap = torch.full((units,), slots, dtype=torch.int32, device="cuda")
+    cap[0] = slots - 2  # two slots of the first unit's region are not its own
+    off = torch.arange(units, dtype=torch.int64, device="cuda") * slots * 2 * blk * d * 2
+    out = torch.empty(units, G, d, device="cuda")
+    wsb = ss.ss_sparse_attention_workspace(units, G, 1, d, blk, k)
+    ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device="cuda")
+    print(f"[gpu] attention: {units} units, G {G}, blk {blk}, k {k}", flush=True)
+    ss.ss_sparse_attention(q, kv, off, sel, cap, slots, units, G, 1, d, blk, k, d ** -0.5, out, ws, wsb)
+    worst = 0.0
+    for u in range(units):
+        s = sel[u][(sel[u] >= 0) & (sel[u] < cap[u])].long()
+        if s.numel() == 0:
+            assert bool((out[u] == 0).all())
+            continue
+        K = kv[u, s, 0].reshape(-1, d).double()
+        V = kv[u, s, 1].view(-1, d, blk).transpose(1, 2).reshape(-1, d).double()
+        p = ((q[u].double() @ K.t().contiguous()) * d ** -0.5).softmax(-1)
+        worst = max(worst, float((out[u].double() - p @ V).abs().max()))
+    assert worst <= 2.0 ** -15 * float(kv.abs().max()), worst
