@@ -12,38 +12,44 @@
 // fp32 and accumulate in fp32.  The GQA heads fill the MFMA rows (padded to
 // 16 with zero weights); each column is one block.
 //
-// Each wave reads a tile of 16 consecutive metadata rows as whole contiguous
-// 1 KiB pieces with the non-temporal cache policy, stages it in LDS and reads
-// its MFMA B fragments from there; there is no cross-lane reduction, the head
-// maximum is taken over accumulator registers.  On MI355X the 128k-token
-// batch streams at 0.82 of the 8 TB/s peak this way.  Fragments loaded
-// straight from HBM (each instruction covering 64-byte pieces of 16 rows)
-// reached 0.765 and got slower with the non-temporal policy, since a
-// 128-byte line was then requested by two instructions; staged through LDS
-// with the default policy they reached 0.765 too.
+// HBM bounds it.  Each wave reads one tile of 16 consecutive metadata rows as
+// whole contiguous 1 KiB pieces with the non-temporal cache policy, stages it
+// in LDS and reads its MFMA B fragments from there; there is no cross-lane
+// reduction, the head maximum is taken over accumulator registers.  Fragments
+// loaded straight from HBM (each instruction covering 64-byte pieces of 16
+// rows) reached 0.765 of the 8 TB/s peak on the 128k-token batch and got
+// slower with the non-temporal policy, since a 128-byte line was then
+// requested by two instructions; staged with the default policy 0.765 too.
 //
-// For cuboid rows the launch reserves LDS up to kResidencyLds per workgroup,
-// so that at most two workgroups (8 waves) share a CU: 0.82 that way against
-// 0.81 with four.  (With direct fragment loads, before the staging: 0.765
-// with two, 0.73 with the eight the registers allow, 0.75 with three, 0.69
-// with one.)  Mean-key rows are half as long and launch with no reservation.
+// Workgroups are two waves of one tile each, so the last workgroups of a
+// launch are short and a ragged batch leaves no CU with a long rest; seven of
+// them a CU keep as many bytes in flight as the eight waves of double-buffered
+// tiles, four tiles a wave, that this replaces.  Dispatch events, us, before
+// and now: 64 sequences x 8 heads x 8192 blocks 330, 317 (6.8 TB/s); the same
+// with 1024 to 8192 blocks 225, 176; 32 x 8 x 2048 blocks 41, 38.7; 11 x 4 x
+// 1024 to 8192 24.2, 20.0; mean keys of 16 x 8 x 256 to 2048 11.0, 8.6; 2 x 2 x
+// 256 5.0, 4.1.  Workgroups of one, four and eight such waves: 330, 330 and 341
+// us for the first, 31.9, 32.4 and 41.4 against 31.4 for 20 x 8 x 512 to 4096.
+// Giving each XCD runs of 512 KiB left the first at 317 and slowed the ragged
+// ones to 205 and 42.
 #include "internal.hpp"
 
 namespace {
 
 constexpr int D = ss::kHeadDim;
-constexpr int TILE = 16;              // blocks per MFMA tile
-constexpr int WAVES = 4;
-constexpr int TILES_PER_WAVE = 4;
-constexpr int BLOCKS_PER_WG = TILE * WAVES * TILES_PER_WAVE;  // 256
-// 2 x 54 KiB fit in a CU's 160 KiB of LDS and 3 do not; the 52 KiB left over
-// still take one attention workgroup (50.5 KiB) beside two scoring workgroups
-constexpr size_t kResidencyLds = 54 * 1024;
-// static LDS of the staging buffers for `row` bytes per metadata row
-constexpr size_t stage_bytes(int row) { return (size_t)WAVES * TILE * (row / 16 + 1) * 16; }
-static_assert(stage_bytes(512) <= kResidencyLds, "staging exceeds the residency budget");
+constexpr int TILE = 16;  // blocks per MFMA tile, one tile per wave
+constexpr int WAVES = 2;
+constexpr int BLOCKS_PER_WG = TILE * WAVES;
 constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gfx9 (32-bit data)
 constexpr int kStream = 2;                // cache policy of the metadata loads: non-temporal
+// Cuboid workgroups take 16.5 KiB of LDS, nine to a CU.  A launch that does
+// not fit at once reserves 22 KiB for each, seven to a CU: 64 x 8 x 8192 blocks
+// 317 us against 322, 32 x 8 x 8192 155 against 159 (six: 314 and 153, but 7.2
+// us against 6.5 for one sequence and 32.5 against 31.7 for 20 ragged ones).
+// Mean-key rows are half as long and launch with no reservation.
+constexpr size_t kResidencyLds = 22 * 1024;
+constexpr int kResident = 9 * 256;
+constexpr size_t kStageBytes = (size_t)WAVES * TILE * (512 + 16);
 
 union frag_t {
     bf16x8_t v;
@@ -60,28 +66,44 @@ union frag_t {
 // KIND 1, mean-key rows (256 B, NCH = 4): each chunk multiplies q itself.
 // AGG 0 takes the maximum over the group's heads, AGG 1 their sum.
 template <int KIND, int AGG>
-__global__ __launch_bounds__(256) void score_kernel(const uint16_t *__restrict__ q,
-                                                    const uint8_t *__restrict__ meta,
-                                                    const int32_t *__restrict__ nblk, int Hq, int Hkv, int G,
-                                                    int nblk_max, int chunks_per_unit, float *__restrict__ scores)
+__global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__restrict__ q,
+                                                           const uint8_t *__restrict__ meta,
+                                                           const int32_t *__restrict__ nblk, int Hq, int Hkv, int G,
+                                                           int nblk_max, int chunks_per_unit,
+                                                           float *__restrict__ scores)
 {
     constexpr int NCH = KIND == 0 ? 8 : 4;
-    constexpr int ROW = NCH * 4 * 16;  // 512 or 256 bytes
+    constexpr int ROW = NCH * 4 * 16;        // 512 or 256 bytes
+    constexpr int NLD = TILE * ROW / 1024;   // 1 KiB loads per tile
+    constexpr int RU = ROW / 16;             // 16-byte units per row
+    constexpr int LR = RU + 1;               // LDS row pitch in 16-byte units
+    // the row pitch is padded by 16 B, so each 16-lane group of a fragment
+    // read touches 64 distinct banks
+    __shared__ uint4 stage[WAVES][TILE * LR];
     const int u = blockIdx.x / chunks_per_unit;
     const int chunk = blockIdx.x - u * chunks_per_unit;
     const int b = u / Hkv, g = u - b * Hkv;
     int n = nblk[b];
     n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
-    const int j0 = chunk * BLOCKS_PER_WG;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j0 = chunk * BLOCKS_PER_WG + wave * TILE;
     if (j0 >= n) return;
 
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
     const int L = lane >> 4;
     const int col = lane & 15;
 
-    // weights of head g*G + col for chunks L*NCH .. L*NCH+NCH-1, selected
-    // branch-free with masks on the 32-bit words (two bf16 each)
+    const uint8_t *mu = meta + (int64_t)u * nblk_max * ROW;
+    // n * ROW <= kMaxBlocks * 512 bytes < 2^31
+    const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc((void *)mu, (short)0, n * ROW, kBufferFlags);
+    uint4 r[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i)  // rows at or past n read as zero (buffer bounds) and are not stored
+        r[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             mrs, (uint32_t)j0 * ROW + lane * 16 + i * 1024, 0, kStream));
+
+    // weights of head g*G + col for chunks 4*m + L, selected branch-free with
+    // masks on the 32-bit words (two bf16 each)
     frag_t w[NCH];
     {
         const bool live = col < G;
@@ -106,68 +128,33 @@ __global__ __launch_bounds__(256) void score_kernel(const uint16_t *__restrict__
         }
     }
 
-    const uint8_t *mu = meta + (int64_t)u * nblk_max * ROW;
-    float *su = scores + (int64_t)u * nblk_max;
-    // n * ROW <= kMaxBlocks * 512 bytes < 2^31
-    const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc((void *)mu, (short)0, n * ROW, kBufferFlags);
-
-    // each wave stages its 16-row tile through its own LDS region: eight (cuboid)
-    // or four (mean key) contiguous 1 KiB non-temporal loads, then the MFMA
-    // fragments are read back (row pitch padded by 16 B, so each 16-lane group
-    // of a fragment read touches 64 distinct banks); the waves interleave over
-    // tiles, so the workgroup walks its rows front to back
-    constexpr int NLD = TILE * ROW / 1024;
-    constexpr int RU = ROW / 16;  // 16-byte units per row
-    constexpr int LR = RU + 1;    // LDS row pitch in 16-byte units
-    __shared__ uint4 stage[WAVES][TILE * LR];
     uint4 *my = stage[wave];
-    const int lane_id = threadIdx.x & 63;
-    uint4 buf[2][NLD];
-    auto load_tile = [&](int t, uint4 *r) {
-        const uint32_t base = (uint32_t)(j0 + (t * WAVES + wave) * TILE) * ROW + lane_id * 16;
 #pragma unroll
-        for (int i = 0; i < NLD; ++i)  // rows at or past n read as zero (buffer bounds) and are not stored
-            r[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(mrs, base + i * 1024, 0, kStream));
-    };
-
-    int ntiles = 0;
-    for (int t = 0; t < TILES_PER_WAVE; ++t)
-        if (j0 + (t * WAVES + wave) * TILE < n) ntiles = t + 1;
-    if (ntiles == 0) return;
-
-    load_tile(0, buf[0]);
-#pragma unroll
-    for (int t = 0; t < TILES_PER_WAVE; ++t) {
-        if (t >= ntiles) break;
-        if (t + 1 < ntiles) load_tile(t + 1, buf[(t + 1) & 1]);
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            const int e = i * 64 + lane_id;
-            my[(e / RU) * LR + e % RU] = buf[t & 1][i];
-        }
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int m = 0; m < NCH; ++m) {
-            frag_t f;
-            f.u = my[col * LR + 4 * m + L];
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m].v, f.v, acc, 0, 0, 0);
-        }
-        float s;
-        if (AGG == 0) {
-            s = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (L * 4 + i < G) s = fmaxf(s, acc[i]);
-            s = fmaxf(s, __shfl_xor(s, 16));
-            s = fmaxf(s, __shfl_xor(s, 32));
-        } else {
-            s = (acc[0] + acc[1]) + (acc[2] + acc[3]);  // padded heads hold exact zeros
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
-        }
-        const int j = j0 + (t * WAVES + wave) * TILE + col;
-        if (L == 0 && j < n) su[j] = s;
+    for (int i = 0; i < NLD; ++i) {
+        const int e = i * 64 + lane;
+        my[(e / RU) * LR + e % RU] = r[i];
     }
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < NCH; ++m) {
+        frag_t f;
+        f.u = my[col * LR + 4 * m + L];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m].v, f.v, acc, 0, 0, 0);
+    }
+    float s;
+    if (AGG == 0) {
+        s = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (L * 4 + i < G) s = fmaxf(s, acc[i]);
+        s = fmaxf(s, __shfl_xor(s, 16));
+        s = fmaxf(s, __shfl_xor(s, 32));
+    } else {
+        s = (acc[0] + acc[1]) + (acc[2] + acc[3]);  // padded heads hold exact zeros
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+    }
+    if (L == 0 && j0 + col < n) scores[(int64_t)u * nblk_max + j0 + col] = s;
 }
 
 }  // namespace
@@ -180,19 +167,16 @@ ss_status launch_score(const void *q, const void *meta, int meta_kind, int agg, 
     const int chunks = (nblk_max + BLOCKS_PER_WG - 1) / BLOCKS_PER_WG;
     const int64_t grid = (int64_t)B * Hkv * chunks;
     if (grid == 0) return SS_OK;
-    SS_CHECK_SUPPORTED(grid <= 0x7FFFFFFF, "score: grid too large");
+    SS_CHECK_SUPPORTED(grid * WAVES * 64 <= 0xFFFFFFFFll, "score: grid too large");
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *mm = static_cast<const uint8_t *>(meta);
-    const dim3 gr((unsigned)grid), bl(256);
+    const dim3 gr((unsigned)grid), bl(WAVES * 64);
     const int G = Hq / Hkv;
-    if (meta_kind == SS_META_CUBOID && agg == SS_AGG_MAX)
-        ss::launch_lds(score_kernel<0, 0>, gr, bl, kResidencyLds - stage_bytes(512), s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
-    else if (meta_kind == SS_META_CUBOID)
-        ss::launch_lds(score_kernel<0, 1>, gr, bl, kResidencyLds - stage_bytes(512), s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
-    else if (agg == SS_AGG_MAX)
-        ss::launch_lds(score_kernel<1, 0>, gr, bl, 0, s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
-    else
-        ss::launch_lds(score_kernel<1, 1>, gr, bl, 0, s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
+    auto *kernel = score_kernel<0, 0>;
+    if (meta_kind == SS_META_CUBOID) kernel = agg == SS_AGG_MAX ? score_kernel<0, 0> : score_kernel<0, 1>;
+    else kernel = agg == SS_AGG_MAX ? score_kernel<1, 0> : score_kernel<1, 1>;
+    const bool cap = meta_kind == SS_META_CUBOID && grid > kResident;
+    ss::launch_lds(kernel, gr, bl, cap ? kResidencyLds - kStageBytes : 0, s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
     return check_launch("ss_score_blocks");
 }
 

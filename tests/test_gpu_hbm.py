@@ -567,3 +567,37 @@ def test_attention_launch_shapes(ss, units, G, blk, k):
         p = ((q[u].double() @ K.t().contiguous()) * d ** -0.5).softmax(-1)
         worst = max(worst, float((out[u].double() - p @ V).abs().max()))
     assert worst <= 2.0 ** -15 * float(kv.abs().max()), worst
+
+
+@pytest.mark.parametrize("kind,agg", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("nblk,G", [((1, 15, 0), 1), ((16, 17, 31), 4), ((33, 48, 32), 7), ((1000, 40, 999), 16),
+                                    ((40000, 65, 39985), 2)])
+def test_score_tile_edges(ss, kind, agg, nblk, G):
+    """Block counts on either side of a tile (16) and of a workgroup (32),
+    sequences that end before a workgroup begins, and a launch of more
+    workgroups than the chip holds at once (two heads of 40000 blocks).
+    Against float64 on the GPU within the summation bound of 256 exact
+    products; scores past a sequence's count keep what they held."""
+    B, Hkv, n, d = len(nblk), 2, max(nblk), 128
+    g = torch.Generator(device="cuda").manual_seed(n * 8 + G)
+    lo = torch.randn(B, Hkv, n, d, generator=g, device="cuda").bfloat16()
+    meta = lo if kind else torch.stack([lo, (lo.float() + torch.rand(lo.shape, generator=g, device="cuda")).bfloat16()], 3)
+    q = torch.randn(B, Hkv * G, d, generator=g, device="cuda").bfloat16()
+    nb = torch.tensor(nblk, dtype=torch.int32, device="cuda")
+    scores = torch.full((B, Hkv, n), 7.5, device="cuda")
+    print(f"[gpu] scores of {nblk} blocks, G {G}, kind {kind}, agg {agg}", flush=True)
+    ss.ss_score_blocks_variant(q, meta.contiguous(), kind, agg, nb, B, Hkv * G, Hkv, n, d, scores)
+    w = q.double().view(B, Hkv, G, d)
+    if kind:
+        per, mag = torch.matmul(lo.double(), w.transpose(2, 3).contiguous()), lo.double().abs()
+    else:
+        m = meta.double()
+        per = torch.matmul(m[:, :, :, 0], w.clamp(max=0).transpose(2, 3).contiguous())
+        per += torch.matmul(m[:, :, :, 1], w.clamp(min=0).transpose(2, 3).contiguous())
+        mag = m.abs().amax(3)
+    want = per.sum(-1) if agg else per.amax(-1)
+    bound = (2 * d + G) * 2.0 ** -24 * torch.matmul(mag, w.abs().transpose(2, 3).contiguous()).sum(-1)
+    for b in range(B):
+        k = nblk[b]
+        assert bool(((scores[b, :, :k].double() - want[b, :, :k]).abs() <= bound[b, :, :k]).all())
+        assert bool((scores[b, :, k:] == 7.5).all())
