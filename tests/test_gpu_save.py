@@ -203,3 +203,34 @@ def test_full_size_128k_shape(ss, oracle_impl):
         assert np.all(c.nblk_o >= 8191)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("blk,Hkv,lens,n_new,threads,shift", [(8, 2, [0, 5, 8], 37, 3, 0), (16, 3, [9, 0], 8, 1, 0),
+                                                              (16, 2, [3, 16, 31, 40], 7, 8, 0),
+                                                              (32, 1, [31, 1], 700, 8, 0), (16, 8, [13], 5000, 8, 0),
+                                                              (8, 8, [0], 4096, 5, 0), (16, 2, [6, 0], 50, 2, 4),
+                                                              (16, 8, [1, 2, 3], 1, 2, 0)])
+def test_save_runs_and_chunks(ss, oracle_impl, blk, Hkv, lens, n_new, threads, shift):
+    """Runs of tokens that start and end anywhere in a block (groups of 8
+    tokens and what is left beside them), several sequences, saves of one and
+    of several copies shared by several threads, and records that are not
+    16-byte aligned (`shift`); bytes outside the saved tokens are untouched."""
+    from paper_2509_24626_amd import harness as H
+    B, rb = len(lens), 2 * blk * D * 2
+    blocks = max(lens) // blk + n_new // blk + 2
+    pool = H.HostPool(B * Hkv * blocks * rb + 16)
+    pool.u8[:] = np.frombuffer(np.random.default_rng(blk + n_new).bytes(pool.nbytes), np.uint8)
+    want = pool.u8.copy()
+    off = np.arange(B * Hkv, dtype=np.int64) * blocks * rb + shift
+    cap = np.full(B, blocks, np.int32)
+    saver = ss.ss_kv_saver_create(B, Hkv, blk, D, pool.host, off, cap, n_new, 2, threads)
+    try:
+        for s in range(3):  # the third save waits for the first one's staging buffer
+            kv = bf16_bits((B, n_new, Hkv, 2, D), torch.Generator().manual_seed(100 * s + blk))
+            ss.ss_kv_save(saver, torch.from_numpy(kv.view(np.int16)).cuda(), n_new, np.asarray(lens, np.int32))
+            ss.ss_kv_save_wait(saver)
+            oracle_impl.save(kv, np.asarray(lens, np.int32), blk, want, off, cap)
+            np.testing.assert_array_equal(pool.u8, want)
+    finally:
+        ss.ss_kv_saver_destroy(saver)
+        pool.close()
