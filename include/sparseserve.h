@@ -87,7 +87,8 @@ ss_status ss_host_free(void *host_ptr);
 /* Measurement hook (not part of the method).  The next kernel that the
  * calling thread launches through this library -- the scoring, top-k,
  * gather, attention or metadata kernel of the next call that launches one;
- * for a split attention, its first kernel only -- records `start_event`
+ * for a split attention, its first kernel only; ss_score_topk scores and
+ * selects rows of at most 256 blocks in one kernel where it can -- records `start_event`
  * (may be NULL) when it starts executing and `stop_event` (may be NULL)
  * when it finishes, as hipExtLaunchKernel does: kernel execution time
  * without the queue's dispatch latency.  Events are hipEvent_t created by

@@ -32,16 +32,13 @@
 // us for the first, 31.9, 32.4 and 41.4 against 31.4 for 20 x 8 x 512 to 4096.
 // Giving each XCD runs of 512 KiB left the first at 317 and slowed the ragged
 // ones to 205 and 42.
-#include "internal.hpp"
+#include "score_tile.hpp"
 
 namespace {
 
-constexpr int D = ss::kHeadDim;
-constexpr int TILE = 16;  // blocks per MFMA tile, one tile per wave
+constexpr int TILE = ss::kTile;  // one tile per wave
 constexpr int WAVES = 2;
 constexpr int BLOCKS_PER_WG = TILE * WAVES;
-constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gfx9 (32-bit data)
-constexpr int kStream = 2;                // cache policy of the metadata loads: non-temporal
 // Cuboid workgroups take 16.5 KiB of LDS, nine to a CU.  A launch that does
 // not fit at once reserves 22 KiB for each, seven to a CU: 64 x 8 x 8192 blocks
 // 317 us against 322, 32 x 8 x 8192 155 against 159 (six: 314 and 153, but 7.2
@@ -49,22 +46,8 @@ constexpr int kStream = 2;                // cache policy of the metadata loads:
 // Mean-key rows are half as long and launch with no reservation.
 constexpr size_t kResidencyLds = 22 * 1024;
 constexpr int kResident = 9 * 256;
-constexpr size_t kStageBytes = (size_t)WAVES * TILE * (512 + 16);
+constexpr size_t kStageBytes = (size_t)WAVES * ss::tile_shape<0>::STAGE * 16;
 
-union frag_t {
-    bf16x8_t v;
-    uint4 u;
-    uint16_t h[8];
-};
-
-// Lane (L = lane/16, col = lane%16) reads 16-byte chunk c = 4*m + L of
-// metadata row `col` of the staged tile for MFMA m.  The A fragments hold
-// the matching weights of head `col`.
-//
-// KIND 0, cuboid rows [lo, hi] (512 B, NCH = 8): chunks 0..15 are lo and
-// multiply min(q, 0), chunks 16..31 (m >= 4) are hi and multiply max(q, 0).
-// KIND 1, mean-key rows (256 B, NCH = 4): each chunk multiplies q itself.
-// AGG 0 takes the maximum over the group's heads, AGG 1 their sum.
 template <int KIND, int AGG>
 __global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__restrict__ q,
                                                            const uint8_t *__restrict__ meta,
@@ -72,14 +55,7 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__res
                                                            int nblk_max, int chunks_per_unit,
                                                            float *__restrict__ scores)
 {
-    constexpr int NCH = KIND == 0 ? 8 : 4;
-    constexpr int ROW = NCH * 4 * 16;        // 512 or 256 bytes
-    constexpr int NLD = TILE * ROW / 1024;   // 1 KiB loads per tile
-    constexpr int RU = ROW / 16;             // 16-byte units per row
-    constexpr int LR = RU + 1;               // LDS row pitch in 16-byte units
-    // the row pitch is padded by 16 B, so each 16-lane group of a fragment
-    // read touches 64 distinct banks
-    __shared__ uint4 stage[WAVES][TILE * LR];
+    __shared__ uint4 stage[WAVES][ss::tile_shape<KIND>::STAGE];
     const int u = blockIdx.x / chunks_per_unit;
     const int chunk = blockIdx.x - u * chunks_per_unit;
     const int b = u / Hkv, g = u - b * Hkv;
@@ -90,71 +66,8 @@ __global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__res
     if (j0 >= n) return;
 
     const int lane = threadIdx.x & 63;
-    const int L = lane >> 4;
-    const int col = lane & 15;
-
-    const uint8_t *mu = meta + (int64_t)u * nblk_max * ROW;
-    // n * ROW <= kMaxBlocks * 512 bytes < 2^31
-    const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc((void *)mu, (short)0, n * ROW, kBufferFlags);
-    uint4 r[NLD];
-#pragma unroll
-    for (int i = 0; i < NLD; ++i)  // rows at or past n read as zero (buffer bounds) and are not stored
-        r[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                             mrs, (uint32_t)j0 * ROW + lane * 16 + i * 1024, 0, kStream));
-
-    // weights of head g*G + col for chunks 4*m + L, selected branch-free with
-    // masks on the 32-bit words (two bf16 each)
-    frag_t w[NCH];
-    {
-        const bool live = col < G;
-        const uint16_t *qh = q + ((int64_t)b * Hq + g * G + (live ? col : 0)) * D;
-        const uint32_t live_mask = live ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-        for (int m = 0; m < NCH; ++m) {
-            const bool hi_half = KIND == 0 && m >= 4;  // cuboid chunks 16..31 multiply hi
-            const int c = (4 * m + L) & 15;            // q channels c*8 .. c*8+7
-            const uint4 x = *reinterpret_cast<const uint4 *>(qh + c * 8);
-            uint32_t v[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                uint32_t keep = live_mask;
-                if (KIND == 0) {
-                    const uint32_t neg = ((v[i] >> 15) & 0x00010001u) * 0xFFFFu;  // 0xFFFF per negative half
-                    keep &= hi_half ? ~neg : neg;  // hi keeps max(q, 0), lo keeps min(q, 0)
-                }
-                v[i] &= keep;
-            }
-            w[m].u = make_uint4(v[0], v[1], v[2], v[3]);
-        }
-    }
-
-    uint4 *my = stage[wave];
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-        const int e = i * 64 + lane;
-        my[(e / RU) * LR + e % RU] = r[i];
-    }
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int m = 0; m < NCH; ++m) {
-        frag_t f;
-        f.u = my[col * LR + 4 * m + L];
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m].v, f.v, acc, 0, 0, 0);
-    }
-    float s;
-    if (AGG == 0) {
-        s = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (L * 4 + i < G) s = fmaxf(s, acc[i]);
-        s = fmaxf(s, __shfl_xor(s, 16));
-        s = fmaxf(s, __shfl_xor(s, 32));
-    } else {
-        s = (acc[0] + acc[1]) + (acc[2] + acc[3]);  // padded heads hold exact zeros
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-    }
-    if (L == 0 && j0 + col < n) scores[(int64_t)u * nblk_max + j0 + col] = s;
+    const float v = ss::score_tile<KIND, AGG>(q, meta, b, g, u, n, j0, Hq, G, nblk_max, stage[wave]);
+    if (lane < TILE && j0 + lane < n) scores[(int64_t)u * nblk_max + j0 + lane] = v;
 }
 
 }  // namespace

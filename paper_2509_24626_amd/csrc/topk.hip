@@ -10,9 +10,9 @@
 //
 // The selection is every key above a bound and the first `quota` keys equal
 // to it.  To find the bound (m = min(k, n) keys wanted):
-//   - one wave: bit by bit from the highest
-//     bit in which the keys differ, counting the keys at or above the trial
-//     value with ballots, until exactly the wanted number is;
+//   - one wave: bit by bit from the highest bit in which the keys differ,
+//     counting the keys at or above the trial value with ballots, until
+//     exactly the wanted number is;
 //   - several waves: the range of the keys is cut into 256 equal intervals
 //     (a shift of key - lowest key) and counted into them in LDS; the interval
 //     of the m-th largest key holds few of them (about ten of 8192 Gaussian
@@ -37,7 +37,7 @@
 // 14.4; 200 distinct values, 256 of 2048: 6.6, 7.7.
 #include <climits>
 
-#include "internal.hpp"
+#include "score_tile.hpp"
 
 namespace {
 
@@ -129,6 +129,96 @@ __device__ __forceinline__ bound_t search(const uint32_t (&off)[N], uint32_t lo,
     return {lo + t, want - c};
 }
 
+// The bound of the m largest of one wave's keys, m below their number; lo, hi:
+// the smallest key - 1 and the complement of the largest.
+template <int R>
+__device__ __forceinline__ bound_t bound_of_wave(const uint32_t (&key)[R], uint32_t lo, uint32_t hi, int m)
+{
+    lo = uniform(lo) + 1u;
+    uint32_t off[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) off[i] = key[i] ? key[i] - lo : 0u;
+    return search(off, lo, ~uniform(hi) - lo, m);
+}
+
+// smallest key - 1 and complement of the largest key over the wave (padding wraps to the largest)
+template <int R>
+__device__ __forceinline__ void key_range(const uint32_t (&key)[R], uint32_t &lo, uint32_t &hi)
+{
+    lo = 0xFFFFFFFFu;
+    hi = 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        lo = min(lo, key[i] - 1u);
+        hi = min(hi, ~key[i]);
+    }
+    lo = wave_min(lo);
+    hi = wave_min(hi);
+}
+
+template <int NW, int R>
+struct place_t {
+    unsigned long long map[2][NW][R];
+    int tot[2][NW];
+};
+
+// Writes the unit's selection (and its copy) in block order.  The lanes hand
+// the selected scores' bits to the lane that owns R consecutive ones (all of
+// them this wave's own, so the waves exchange only their totals); a scan of
+// the lanes' bit counts places each lane's first output.  A key equal to the
+// bound is taken if fewer than `quota` of them come before it.
+template <int NW, int R>
+__device__ __forceinline__ void place(const uint32_t (&key)[R], bound_t bound, int m, int wave, int lane, int32_t *out,
+                                      int32_t *out2, place_t<NW, R> &sm)
+{
+    typedef typename bits_of<R>::type bits_t;
+    auto hand_over = [&](int which, auto taken) -> bits_t {
+        uint32_t lo = 0, hi = 0;
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const unsigned long long mask = __ballot(taken(key[i]));
+            lo = lane == i ? (uint32_t)mask : lo;
+            hi = lane == i ? (uint32_t)(mask >> 32) : hi;
+            c += __popcll(mask);
+        }
+        if (lane < R) sm.map[which][wave][lane] = (unsigned long long)hi << 32 | lo;
+        if (lane == 0) sm.tot[which][wave] = c;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (R == 64) {
+            return sm.map[which][wave][lane];
+        } else {
+            const uint32_t w = reinterpret_cast<const uint32_t *>(sm.map[which][wave])[lane * R / 32];
+            return (w >> (lane * R % 32)) & ((1u << R) - 1u);
+        }
+    };
+    bits_t bits = hand_over(0, [&](uint32_t x) { return x > bound.above; }), eq_bits = 0;
+    if (bound.quota) eq_bits = hand_over(1, [&](uint32_t x) { return x == bound.above; });
+    int pos = wave_scan(popcount(bits)) - popcount(bits);
+    if constexpr (NW > 1) {
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) pos += w < wave ? sm.tot[0][w] : 0;
+    }
+    if (bound.quota) {
+        int before = wave_scan(popcount(eq_bits)) - popcount(eq_bits);
+        if constexpr (NW > 1) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) before += w < wave ? sm.tot[1][w] : 0;
+        }
+        pos += min(before, bound.quota);
+        int left = max(bound.quota - before, 0);
+        for (bits_t e = eq_bits; e && left > 0; e &= e - 1, --left) bits |= e & (~e + 1);
+    }
+    const int first = (wave * 64 + lane) * R;
+    for (; bits; bits &= bits - 1, ++pos)
+        if (pos < m) {  // always holds; the guard keeps writes in range
+            const int j = first + lowest(bits);
+            out[pos] = j;
+            if (out2) out2[pos] = j;
+        }
+}
+
 template <int NT, int R>
 __global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scores, const int32_t *__restrict__ nblk,
                                                   int Hkv, int nblk_max, int k, int32_t *__restrict__ sel,
@@ -169,21 +259,10 @@ __global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scor
 
     bound_t bound = {0u, 0};  // every key, where all are selected
     if (m < n) {
-        // smallest and largest key (padding wraps to the largest)
-        uint32_t lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu;  // hi: complement
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            lo = min(lo, key[i] - 1u);
-            hi = min(hi, ~key[i]);
-        }
-        lo = wave_min(lo);
-        hi = wave_min(hi);
+        uint32_t lo, hi;
+        key_range(key, lo, hi);
         if constexpr (NW == 1) {
-            lo = uniform(lo) + 1u;
-            uint32_t off[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) off[i] = key[i] ? key[i] - lo : 0u;
-            bound = search(off, lo, ~uniform(hi) - lo, m);
+            bound = bound_of_wave(key, lo, hi, m);
         } else {
             __shared__ uint32_t cand[kCand];
             __shared__ uint32_t red_lo[NW], red_hi[NW];
@@ -294,59 +373,55 @@ __global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scor
         }
     }
 
-    // Output positions in block order.  The lanes hand the selected scores'
-    // bits to the lane that owns R consecutive ones (all of them this wave's
-    // own, so the waves exchange only their totals); a scan of the lanes' bit
-    // counts places each lane's first output.  A key equal to the bound is
-    // taken if fewer than `quota` of them come before it.
-    typedef typename bits_of<R>::type bits_t;
-    __shared__ unsigned long long map[2][NW][R];
-    __shared__ int tot[2][NW];
-    auto hand_over = [&](int which, auto taken) -> bits_t {
-        uint32_t lo = 0, hi = 0;
-        int c = 0;
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const unsigned long long mask = __ballot(taken(key[i]));
-            lo = lane == i ? (uint32_t)mask : lo;
-            hi = lane == i ? (uint32_t)(mask >> 32) : hi;
-            c += __popcll(mask);
+    __shared__ place_t<NW, R> sm;
+    place<NW, R>(key, bound, m, wave, lane, out, out2, sm);
+}
+
+// Scores and selects rows of at most 16*W blocks in one launch: one workgroup
+// per unit, one wave per tile (all of the unit's metadata is in flight at
+// once), then wave 0 selects from the scores in LDS.
+template <int W>
+__global__ __launch_bounds__(W * 64) void score_topk_kernel(const uint16_t *__restrict__ q,
+                                                            const uint8_t *__restrict__ meta,
+                                                            const int32_t *__restrict__ nblk, int Hq, int Hkv, int G,
+                                                            int nblk_max, int k, float *__restrict__ scores,
+                                                            int32_t *__restrict__ sel)
+{
+    constexpr int R = W * ss::kTile / 64;
+    __shared__ uint4 stage[W][ss::tile_shape<SS_META_CUBOID>::STAGE];
+    __shared__ uint32_t row[W * ss::kTile];
+    __shared__ place_t<1, R> sm;
+    const int u = blockIdx.x;
+    const int b = u / Hkv, g = u - b * Hkv;
+    int n = nblk[b];
+    n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j0 = wave * ss::kTile;
+    if (j0 < n) {
+        const float v = ss::score_tile<SS_META_CUBOID, SS_AGG_MAX>(q, meta, b, g, u, n, j0, Hq, G, nblk_max,
+                                                                   stage[wave]);
+        if (lane < ss::kTile) {
+            row[j0 + lane] = __float_as_uint(v);
+            if (j0 + lane < n) scores[(int64_t)u * nblk_max + j0 + lane] = v;
         }
-        if (lane < R) map[which][wave][lane] = (unsigned long long)hi << 32 | lo;
-        if (lane == 0) tot[which][wave] = c;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if constexpr (R == 64) {
-            return map[which][wave][lane];
-        } else {
-            const uint32_t w = reinterpret_cast<const uint32_t *>(map[which][wave])[lane * R / 32];
-            return (w >> (lane * R % 32)) & ((1u << R) - 1u);
-        }
-    };
-    bits_t bits = hand_over(0, [&](uint32_t x) { return x > bound.above; }), eq_bits = 0;
-    if (bound.quota) eq_bits = hand_over(1, [&](uint32_t x) { return x == bound.above; });
-    int pos = wave_scan(popcount(bits)) - popcount(bits);
-    if constexpr (NW > 1) {
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NW; ++w) pos += w < wave ? tot[0][w] : 0;
     }
-    if (bound.quota) {
-        int before = wave_scan(popcount(eq_bits)) - popcount(eq_bits);
-        if constexpr (NW > 1) {
+    __syncthreads();
+    if (wave > 0) return;
+    const int m = k < n ? k : n;
+    int32_t *out = sel + (int64_t)u * k;
+    for (int i = m + lane; i < k; i += 64) out[i] = -1;
+    if (m == 0) return;
+    uint32_t key[R];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) before += w < wave ? tot[1][w] : 0;
-        }
-        pos += min(before, bound.quota);
-        int left = max(bound.quota - before, 0);
-        for (bits_t e = eq_bits; e && left > 0; e &= e - 1, --left) bits |= e & (~e + 1);
+    for (int i = 0; i < R; ++i) key[i] = i * 64 + lane < n ? score_key(row[i * 64 + lane]) : 0u;
+    bound_t bound = {0u, 0};  // every key, where all are selected
+    if (m < n) {
+        uint32_t lo, hi;
+        key_range(key, lo, hi);
+        bound = bound_of_wave(key, lo, hi, m);
     }
-    const int first = (wave * 64 + lane) * R;
-    for (; bits; bits &= bits - 1, ++pos)
-        if (pos < m) {  // always holds; the guard keeps writes in range
-            const int j = first + lowest(bits);
-            out[pos] = j;
-            if (out2) out2[pos] = j;
-        }
+    place<1, R>(key, bound, m, 0, lane, out, nullptr, sm);
 }
 
 template <int NT, int R>
@@ -412,6 +487,21 @@ extern "C" ss_status ss_score_topk(const void *q, const void *meta, const int32_
     if (B == 0) return SS_OK;
     SS_CHECK_ARG(sel, "ss_score_topk: null sel");
     hipStream_t s = ss::as_stream(stream);
+    // One launch where a workgroup per unit holds its whole row in flight: a
+    // launch and the scores' way through memory less.  us a call, two launches
+    // and one: 4 units of 256 blocks 7.5, 5.5; 256 units of 256 10.9, 9.0; 512
+    // of 100 10.2, 7.2; 512 of 64 8.6, 5.7.  16 waves fill a CU, so beyond one
+    // unit a CU the selections no longer hide under other units' loads (512
+    // units of 256 blocks 15.8, 16.7).
+    if (nblk_max >= 1 && (nblk_max <= 8 * ss::kTile || (nblk_max <= 16 * ss::kTile && B * Hkv <= 256))) {
+        auto *kernel = score_topk_kernel<16>;
+        int waves = 16;
+        if (nblk_max <= 4 * ss::kTile) kernel = score_topk_kernel<4>, waves = 4;
+        else if (nblk_max <= 8 * ss::kTile) kernel = score_topk_kernel<8>, waves = 8;
+        ss::launch(kernel, dim3(B * Hkv), dim3(waves * 64), s, static_cast<const uint16_t *>(q),
+                   static_cast<const uint8_t *>(meta), nblk, Hq, Hkv, Hq / Hkv, nblk_max, k, scores, sel);
+        return ss::check_launch("ss_score_topk");
+    }
     st = ss::launch_score(q, meta, SS_META_CUBOID, SS_AGG_MAX, nblk, B, Hq, Hkv, nblk_max, scores, s);
     if (st != SS_OK) return st;
     return ss::launch_topk(scores, nblk, B, Hkv, nblk_max, k, sel, nullptr, s);

@@ -601,3 +601,28 @@ def test_score_tile_edges(ss, kind, agg, nblk, G):
         k = nblk[b]
         assert bool(((scores[b, :, :k].double() - want[b, :, :k]).abs() <= bound[b, :, :k]).all())
         assert bool((scores[b, :, k:] == 7.5).all())
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257])
+@pytest.mark.parametrize("B,Hkv,G", [(3, 2, 4), (64, 4, 1), (257, 1, 7), (2, 1, 16)])
+def test_score_topk_in_one_launch(ss, n, B, Hkv, G):
+    """ss_score_topk over rows around the lengths that one launch takes, with
+    as many units as CUs and one more, against ss_score_blocks followed by
+    ss_select_topk: scores and selections bit for bit, scores past a count
+    and everything else untouched.  Repeated metadata rows give exact ties;
+    counts of 0, of one block and of all, and more wanted than there are."""
+    d = 128
+    g = torch.Generator(device="cuda").manual_seed(n * 1000 + B)
+    lo = torch.randn(B, Hkv, n, d, generator=g, device="cuda").bfloat16()
+    lo[:, :, n // 2:] = lo[:, :, :n - n // 2]
+    meta = torch.stack([lo, lo + 1], 3).contiguous()
+    q = torch.randn(B, Hkv * G, d, generator=g, device="cuda").bfloat16()
+    nb = torch.randint(0, n + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    nb[0], nb[-1] = n, min(n, 1)
+    for k in sorted({1, max(n // 3, 1), n + 2}):
+        one = torch.full((B, Hkv, n), 7.5, device="cuda"), torch.full((B, Hkv, k), -5, dtype=torch.int32, device="cuda")
+        two = one[0].clone(), one[1].clone()
+        ss.ss_score_topk(q, meta, nb, B, Hkv * G, Hkv, n, d, k, *one)
+        ss.ss_score_blocks(q, meta, nb, B, Hkv * G, Hkv, n, d, two[0])
+        ss.ss_select_topk(two[0], nb, B, Hkv, n, k, two[1])
+        assert torch.equal(one[0], two[0]) and torch.equal(one[1], two[1]), (n, B, Hkv, G, k)
