@@ -36,6 +36,7 @@
 // place of its K tile), and with several splits a second kernel merges the
 // split partials in split order.  All merges run in a fixed order, so results
 // do not depend on scheduling.  plan() says how waves and splits are chosen.
+#include <algorithm>
 #include <mutex>
 #include <unordered_map>
 
@@ -382,15 +383,29 @@ split_plan plan(int units, int k, int blk)
     return {4, (steps + sps - 1) / sps, sps};
 }
 
+// The splits a workspace has to have room for: the plan's, and at least two
+// 4-wave workgroups per CU of 16 steps or more each.  The latter is the size
+// that callers have been told to bring since before units were given whole to
+// 8 waves, so a shape that needs a workspace keeps needing one of that size
+// whichever plan serves it.  units * splits stays below 1024 (fewer than
+// units + 512, with more than one split only below 512 units).
+int workspace_splits(int units, int k, int blk)
+{
+    const int steps = (int)(((int64_t)k * blk + TOK - 1) / TOK);
+    const int want = std::max(1, std::min((512 + units - 1) / units, steps / 16));
+    const int sps = (steps + want - 1) / want;
+    return std::max((steps + sps - 1) / sps, plan(units, k, blk).splits);
+}
+
 }  // namespace
 
 extern "C" size_t ss_sparse_attention_workspace(int B, int Hq, int Hkv, int d, int blk, int k)
 {
     if (B <= 0 || Hkv <= 0 || Hq <= 0 || Hq % Hkv || d != D || !ss::supported_blk(blk) || k <= 0) return 0;
     const int units = B * Hkv;
-    split_plan sp = plan(units, k, blk);
-    if (sp.splits <= 1) return 0;
-    return (size_t)units * sp.splits * (Hq / Hkv) * (D + 2) * sizeof(float);
+    const int splits = workspace_splits(units, k, blk);
+    if (splits <= 1) return 0;
+    return (size_t)units * splits * (Hq / Hkv) * (D + 2) * sizeof(float);
 }
 
 extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, const int64_t *region_off,
