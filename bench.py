@@ -666,21 +666,21 @@ def exit_report():
 # sources of its kernel hash as they did then; otherwise traffic is null.
 KERNEL_SOURCES = {
     "gather": ["gather.hip", "decode.cpp"],
-    "score": ["score.hip"],
-    "topk": ["topk.hip"],
+    "score": ["score.hip", "score_tile.hpp"],
+    "topk": ["topk.hip", "score_tile.hpp"],
     "attention": ["attention.hip"],
 }
 # hierarchical 128k-context layer, seed 0, 20 timed steps (the driver's --steps 20 --warmup 5), groups
 # 2,4,10,20,18,8,2, host resolve
 _KEY = ["hier-b64-ctx128k-blk16-k128-cache25", 0, 20, [2, 4, 10, 20, 18, 8, 2], "host"]
 TRAFFIC = {
-    "gather": {"key": _KEY, "digest": "fc3ee5fdc0ce0be4", "bytes": 245801680, "fetch": 123714256,
+    "gather": {"key": _KEY, "digest": "fc3ee5fdc0ce0be4", "bytes": 245799140, "fetch": 123711716,
               "write": 122087424},
-    "score": {"key": _KEY, "digest": "c9510f2bf97a7ac5", "bytes": 2168521631, "fetch": 2151712671,
-              "write": 16808960},
-    "topk": {"key": _KEY, "digest": "1d38913edab606c6", "bytes": 17217148, "fetch": 16955004,
+    "score": {"key": _KEY, "digest": "1680a2357b44d9cc", "bytes": 2168443840, "fetch": 2151666592,
+              "write": 16777248},
+    "topk": {"key": _KEY, "digest": "2d7010e9dfeee940", "bytes": 17187453, "fetch": 16925309,
               "write": 262144},
-    "attention": {"key": _KEY, "digest": "9e23bba1c2251224", "bytes": 539142308, "fetch": 538093732,
+    "attention": {"key": _KEY, "digest": "c3ccd0d8227ef76d", "bytes": 539150436, "fetch": 538101860,
               "write": 1048576},
 }
 
