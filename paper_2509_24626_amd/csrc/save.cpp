@@ -317,12 +317,17 @@ ss_status ss_kv_save(ss_kv_saver *sv, const void *new_kv, int n_new, const int32
     const int64_t rows = (int64_t)sv->B * n_new;
     const size_t total = (size_t)rows * sv->row_bytes;
     const int want = std::min(kMaxChunks, std::max(1, (int)std::sqrt((double)total / kChunkBytes)));
-    // ends of chunks and of the threads' shares fall on whole blocks where sequences start on them
-    const auto whole = [&](int64_t n) { return std::max<int64_t>(1, n > sv->blk ? n / sv->blk * sv->blk : n); };
-    const int64_t per = whole((rows + want - 1) / want + (want > 1 ? sv->blk - 1 : 0));
+    // Ends of chunks and of the threads' shares fall on whole blocks where
+    // sequences start on them.  Saves of fewer tokens than a block (a decode
+    // step's rows are sequences) have no such ends, and one copy has none
+    // inside it: cut off at the last whole block, the rest was a second copy
+    // of a few rows, for another 15 us.
+    const int64_t unit = n_new >= sv->blk ? sv->blk : 1;
+    const auto whole = [&](int64_t n) { return std::max<int64_t>(1, n > unit ? n / unit * unit : n); };
+    const int64_t per = want == 1 ? rows : whole((rows + want - 1) / want + unit - 1);
     const int n_chunks = (int)((rows + per - 1) / per);
     const int64_t least = (int64_t)((kItemBytes + sv->row_bytes - 1) / sv->row_bytes);
-    const int64_t share = whole(std::max(least, (per + sv->threads - 1) / sv->threads + sv->blk - 1));
+    const int64_t share = whole(std::max(least, (per + sv->threads - 1) / sv->threads + unit - 1));
     const uint8_t *src = static_cast<const uint8_t *>(new_kv);
     uint8_t *dst = static_cast<uint8_t *>(sv->staging[slot]);
     for (int c = 0; c < n_chunks; ++c) {
