@@ -306,8 +306,12 @@ ss_status ss_gather_blocks(const int32_t *miss, int64_t n_miss, const void *pool
  *   block cache's capacities), or NULL to bound every unit by slot_limit
  *   slot_limit: the largest slot count of any unit (slot_limit records
  *   must span less than 2 GiB; SS_ERR_UNSUPPORTED otherwise)
- *   workspace: device, at least ss_sparse_attention_workspace(...) bytes
- *   (the call fails with SS_ERR_OOM if ws_bytes is smaller).
+ *   workspace: device, ss_sparse_attention_workspace(...) bytes, in which
+ *   the call splits the selection as far as that pays.  A smaller one is
+ *   taken with fewer splits (and another order of the sums), down to the
+ *   partials of max(1, min(ceil(512 / units), steps / 16)) splits of the
+ *   steps = ceil(k * blk / 16) of each of the units = B*Hkv; the call fails
+ *   with SS_ERR_OOM below that.
  * All-HBM layouts pass slots = the selection, region_off = the units'
  * block arrays, capacity = NULL and slot_limit = nblk_max. */
 size_t ss_sparse_attention_workspace(int B, int Hq, int Hkv, int d, int blk, int k);

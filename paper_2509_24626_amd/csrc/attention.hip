@@ -76,6 +76,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+constexpr int kMaxSplits = 32;  // splits of a unit's steps
+
 struct split_plan {
     int waves, splits, steps_per_split;
 };
@@ -362,8 +364,9 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
 // do: a step takes a CU about 0.32 us of the chip's bandwidth, a workgroup
 // costs about 0.012 us, the second launch 4 us (44 units of 256 steps: 5
 // splits 20.7 us, 12 splits 22.5; 264 units of 128 steps: 2 splits 56.5 us, 3
-// splits 52.8).  units * splits stays below 1024, which bounds the partials.
-split_plan plan(int units, int k, int blk)
+// splits 52.8).  units * splits stays below 1024, which bounds the partials,
+// and no more than `most` splits are taken, for which there is room.
+split_plan plan(int units, int k, int blk, int most)
 {
     const int steps = (int)(((int64_t)k * blk + TOK - 1) / TOK);
     if ((units <= 256 && (steps < 32 || units >= 144 || (units >= 96 && steps <= 96))) ||
@@ -371,7 +374,7 @@ split_plan plan(int units, int k, int blk)
         return {8, 1, steps};
     int best = 1;
     float least = 0.f;
-    for (int n = 1; n <= 32 && (n == 1 || (units * n < 1024 && n * (units * n <= CUS ? 4 : 8) <= steps)); ++n) {
+    for (int n = 1; n <= most && (n == 1 || (units * n < 1024 && n * (units * n <= CUS ? 4 : 8) <= steps)); ++n) {
         const float rounds = (float)((units * n + CUS - 1) / CUS);
         const float cost = rounds / n * steps * 0.32f + (n > 1 ? 0.012f * units * n + 4.f : 0.f);
         if (n == 1 || cost < least) {
@@ -383,29 +386,43 @@ split_plan plan(int units, int k, int blk)
     return {4, (steps + sps - 1) / sps, sps};
 }
 
-// The splits a workspace has to have room for: the plan's, and at least two
-// 4-wave workgroups per CU of 16 steps or more each.  The latter is the size
-// that callers have been told to bring since before units were given whole to
-// 8 waves, so a shape that needs a workspace keeps needing one of that size
-// whichever plan serves it.  units * splits stays below 1024 (fewer than
-// units + 512, with more than one split only below 512 units).
-int workspace_splits(int units, int k, int blk)
+// The splits a workspace must have room for: two 4-wave workgroups per CU of
+// 16 steps or more each.  Callers bring that much whichever plan serves the
+// shape; what is refused does not move with the plans.  A plan that wants more
+// is cut to what the workspace holds, and the query asks for the larger of the
+// two.  units * splits stays below 1024 (fewer than units + 512, with more
+// than one split only below 512 units).
+int least_splits(int units, int k, int blk)
 {
     const int steps = (int)(((int64_t)k * blk + TOK - 1) / TOK);
     const int want = std::max(1, std::min((512 + units - 1) / units, steps / 16));
     const int sps = (steps + want - 1) / want;
-    return std::max((steps + sps - 1) / sps, plan(units, k, blk).splits);
+    return (steps + sps - 1) / sps;
 }
+
+bool has_plan(int B, int Hq, int Hkv, int d, int blk, int k)
+{
+    return B > 0 && Hkv > 0 && Hq > 0 && Hq % Hkv == 0 && d == D && ss::supported_blk(blk) && k > 0;
+}
+
+// bytes of the partials of one split of every unit
+size_t split_bytes(int B, int Hq) { return (size_t)B * Hq * (D + 2) * sizeof(float); }
 
 }  // namespace
 
+size_t ss::attention_workspace_least(int B, int Hq, int Hkv, int d, int blk, int k)
+{
+    if (!has_plan(B, Hq, Hkv, d, blk, k)) return 0;
+    const int splits = least_splits(B * Hkv, k, blk);
+    return splits > 1 ? splits * split_bytes(B, Hq) : 0;
+}
+
 extern "C" size_t ss_sparse_attention_workspace(int B, int Hq, int Hkv, int d, int blk, int k)
 {
-    if (B <= 0 || Hkv <= 0 || Hq <= 0 || Hq % Hkv || d != D || !ss::supported_blk(blk) || k <= 0) return 0;
+    if (!has_plan(B, Hq, Hkv, d, blk, k)) return 0;
     const int units = B * Hkv;
-    const int splits = workspace_splits(units, k, blk);
-    if (splits <= 1) return 0;
-    return (size_t)units * splits * (Hq / Hkv) * (D + 2) * sizeof(float);
+    const int splits = std::max(least_splits(units, k, blk), plan(units, k, blk, kMaxSplits).splits);
+    return splits > 1 ? splits * split_bytes(B, Hq) : 0;
 }
 
 extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, const int64_t *region_off,
@@ -426,10 +443,11 @@ extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, con
     SS_CHECK_SUPPORTED(slot_limit >= 0 && (int64_t)slot_limit * 2 * blk * D * 2 <= 0x7FFFFFFF,
                        "ss_sparse_attention: slot_limit=%d records exceed a 2 GiB region", slot_limit);
     const int units = B * Hkv;
-    split_plan sp = plan(units, k, blk);
-    const size_t need = ss_sparse_attention_workspace(B, Hq, Hkv, d, blk, k);
+    const size_t need = ss::attention_workspace_least(B, Hq, Hkv, d, blk, k);
     if (ws_bytes < need || (need && !workspace))
         return ss::fail(SS_ERR_OOM, "ss_sparse_attention: workspace %zu bytes < %zu", ws_bytes, need);
+    const size_t room = workspace ? ws_bytes / split_bytes(B, Hq) : 0;
+    const split_plan sp = plan(units, k, blk, (int)std::min(room, (size_t)kMaxSplits));
     hipStream_t s = ss::as_stream(stream);
     const float scale_log2 = scale * 1.4426950408889634f;
     const dim3 grid(units, sp.splits);

@@ -178,6 +178,26 @@ ss_status record(void *const *events, int i, hipStream_t s)
     return hip_check(hipEventRecord(reinterpret_cast<hipEvent_t>(events[i]), s), "record timing event");
 }
 
+// The attention workspace cut into `regions` for launches that run side by
+// side, *one bytes each: as much as a group of the P makes use of, and what
+// there is where the caller brings less, at least what a group must have.
+template <class F>
+ss_status attention_regions(const ss_layer_buffers *L, int P, const F &b_of, int regions, const char *who, size_t *one)
+{
+    size_t least = 0, use = 0;
+    for (int p = 0; p < P; ++p) {
+        const int Bp = b_of(p + 1) - b_of(p);
+        least = std::max(least, ss::attention_workspace_least(Bp, L->Hq, L->Hkv, L->d, L->blk, L->k));
+        use = std::max(use, ss_sparse_attention_workspace(Bp, L->Hq, L->Hkv, L->d, L->blk, L->k));
+    }
+    least = (least + 255) & ~(size_t)255;
+    use = (use + 255) & ~(size_t)255;
+    if (L->attn_ws_bytes < least * regions || (least && !L->attn_ws))
+        return ss::fail(SS_ERR_OOM, "%s: attention workspace %zu bytes < %zu", who, L->attn_ws_bytes, least * regions);
+    *one = L->attn_ws ? std::min(use, (L->attn_ws_bytes / regions) & ~(size_t)255) : 0;
+    return SS_OK;
+}
+
 }  // namespace
 
 extern "C" ss_status ss_decode_layer(const ss_layer_buffers *L, int64_t step, const void *q, float *out, void *stream,
@@ -333,19 +353,12 @@ extern "C" ss_status ss_decode_layer_dev(const ss_layer_buffers *L, ss_dev_cache
     // attention workspace: one region for the attentions on `stream`, one for
     // those on the compute stream (the two run at the same time)
     size_t ws_one = 0;
-    for (int p = 0; p < P; ++p) {
-        const size_t w = ss_sparse_attention_workspace(b_of(p + 1) - b_of(p), Hq, Hkv, d, L->blk, k);
-        ws_one = w > ws_one ? w : ws_one;
-    }
-    ws_one = (ws_one + 255) & ~(size_t)255;
     const bool comp_attn = P > 2;  // the middle groups attend on the compute stream
-    const size_t ws_need = ws_one * (comp_attn ? 2 : 1);
-    if (L->attn_ws_bytes < ws_need || (ws_need && !L->attn_ws))
-        return ss::fail(SS_ERR_OOM, "ss_decode_layer_dev: attention workspace %zu bytes < %zu", L->attn_ws_bytes,
-                        ws_need);
+    ss_status st = attention_regions(L, P, b_of, comp_attn ? 2 : 1, "ss_decode_layer_dev", &ws_one);
+    if (st) return st;
     char *ws_s = static_cast<char *>(L->attn_ws);
     char *ws_c = ws_s ? ws_s + ws_one : nullptr;
-    ss_status st = ss::dev_cache_check_step(dc, step, k);
+    st = ss::dev_cache_check_step(dc, step, k);
     if (st) return st;
     std::lock_guard<std::mutex> lock(g_exec_mu);
     exec_state *ex = nullptr;
@@ -492,16 +505,7 @@ extern "C" ss_status ss_decode_step_dev(const ss_layer_buffers *const *layers, s
                      l, (long long)L->miss_cap);
         SS_CHECK_ARG(L->meta_kind == SS_META_CUBOID || L->meta_kind == SS_META_MEAN,
                      "ss_decode_step_dev: layer %d: metadata kind %d", l, L->meta_kind);
-        size_t w1 = 0;
-        for (int p = 0; p < P; ++p) {
-            const size_t w = ss_sparse_attention_workspace(b_of(p + 1) - b_of(p), Hq, Hkv, d, L->blk, k);
-            w1 = w > w1 ? w : w1;
-        }
-        w1 = (w1 + 255) & ~(size_t)255;
-        ws_one[l] = w1;
-        if (L->attn_ws_bytes < w1 * NS || (w1 && !L->attn_ws))
-            return ss::fail(SS_ERR_OOM, "ss_decode_step_dev: layer %d: attention workspace %zu bytes < %zu", l,
-                            L->attn_ws_bytes, w1 * NS);
+        if (ss_status w = attention_regions(L, P, b_of, NS, "ss_decode_step_dev", &ws_one[l])) return w;
     }
     ss_status st;
     for (int l = 0; l < n_layers; ++l)
@@ -653,16 +657,7 @@ extern "C" ss_status ss_decode_step(const ss_layer_buffers *const *layers, int n
                      l, (long long)L->miss_cap);
         SS_CHECK_ARG(L->meta_kind == SS_META_CUBOID || L->meta_kind == SS_META_MEAN,
                      "ss_decode_step: layer %d: metadata kind %d", l, L->meta_kind);
-        size_t w1 = 0;
-        for (int p = 0; p < P; ++p) {
-            const size_t w = ss_sparse_attention_workspace(b_of(p + 1) - b_of(p), Hq, Hkv, d, L->blk, k);
-            w1 = w > w1 ? w : w1;
-        }
-        w1 = (w1 + 255) & ~(size_t)255;
-        ws_one[l] = w1;
-        if (L->attn_ws_bytes < w1 * NS || (w1 && !L->attn_ws))
-            return ss::fail(SS_ERR_OOM, "ss_decode_step: layer %d: attention workspace %zu bytes < %zu", l,
-                            L->attn_ws_bytes, w1 * NS);
+        if (ss_status w = attention_regions(L, P, b_of, NS, "ss_decode_step", &ws_one[l])) return w;
         if ((st = device_address(L->sel_host, (void **)&sel_hd[l])) ||
             (st = device_address(L->slots_host, (void **)&slots_hd[l])) ||
             (st = device_address(L->miss_host, (void **)&miss_hd[l])))

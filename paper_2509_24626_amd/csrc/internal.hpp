@@ -35,6 +35,10 @@ ss_status check_score_args(const void *q, const void *meta, const int32_t *nblk,
 ss_status launch_score(const void *q, const void *meta, int meta_kind, int agg, const int32_t *nblk, int B, int Hq,
                        int Hkv, int nblk_max, float *scores, hipStream_t s);
 
+// sparse attention (attention.hip): the least workspace that a call takes; with
+// what ss_sparse_attention_workspace asks for it uses as many splits as pay
+size_t attention_workspace_least(int B, int Hq, int Hkv, int d, int blk, int k);
+
 // f(begin, end) over [0, n) on the library's host worker threads
 void parallel_for(int64_t n, int max_threads, const std::function<void(int64_t, int64_t)> &f);
 

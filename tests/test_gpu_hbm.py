@@ -569,6 +569,33 @@ def test_attention_launch_shapes(ss, units, G, blk, k):
     assert worst <= 2.0 ** -15 * float(kv.abs().max()), worst
 
 
+@pytest.mark.parametrize("units,k,splits", [(8, 128, 8), (4, 100, 7), (16, 511, 31), (24, 128, 8)])
+def test_attention_with_less_workspace(ss, units, k, splits):
+    """A workspace smaller than the query's, down to the least one (two 4-wave
+    workgroups a CU of 16 steps or more each: `splits`), is served with as many
+    splits as it holds: the same output within the 16 bits of a probability,
+    nothing written past the end."""
+    G, blk, d = 4, 16, 128
+    g = torch.Generator(device="cuda").manual_seed(units + k)
+    kv = torch.randn(units, k, 2, blk * d, generator=g, device="cuda").bfloat16()
+    q = torch.randn(units, G, d, generator=g, device="cuda").bfloat16()
+    sel = torch.arange(k, dtype=torch.int32, device="cuda").repeat(units, 1)
+    off = torch.arange(units, dtype=torch.int64, device="cuda") * k * 2 * blk * d * 2
+    one = units * G * (d + 2) * 4
+    full = ss.ss_sparse_attention_workspace(units, G, 1, d, blk, k)
+    assert full >= splits * one
+    got = []
+    for size in (full, (full + splits * one) // 2, splits * one):
+        print(f"[gpu] attention: {units} units, k {k}, workspace {size} of {full}", flush=True)
+        ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.empty(units, G, d, device="cuda")
+        ss.ss_sparse_attention(q, kv, off, sel, None, k, units, G, 1, d, blk, k, d ** -0.5, out, ws, size)
+        assert bool((ws[size:] == 0x5A).all())
+        got.append(out)
+    for out in got[1:]:
+        assert float((out - got[0]).abs().max()) <= 2.0 ** -15 * float(kv.abs().max())
+
+
 @pytest.mark.parametrize("kind,agg", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("nblk,G", [((1, 15, 0), 1), ((16, 17, 31), 4), ((33, 48, 32), 7), ((1000, 40, 999), 16),
                                     ((40000, 65, 39985), 2)])

@@ -226,6 +226,49 @@ def test_groups_schedule_callback_error_and_checks(ss, resolve):
         close(pool, Ls)
 
 
+@pytest.mark.parametrize("resolve", ["device", "host"])
+def test_steps_take_the_least_attention_workspace(ss, resolve):
+    """A workspace of the least size per stream (two 4-wave workgroups a CU of
+    16 steps or more each: 8 splits of 24 units, of which the plan would use
+    10) serves the one-layer step and the groups schedule: the same
+    selections, outputs that differ by the order of the splits' sums alone
+    (every probability keeps 16 bits: 2^-15 of the largest |V|, six sigma of
+    a scale of at most 2), and one byte less is refused."""
+    from paper_2509_24626_amd import harness as H
+    cfg, seed = small_cfg(layers=2), 11
+    dev = resolve == "device"
+    pa, A = build(cfg, seed, 4, dev)
+    pb, Bm = build(cfg, seed, 4, dev)
+    try:
+        one = 8 * 3 * cfg.Hq * 130 * 4
+        assert ss.ss_sparse_attention_workspace(3, cfg.Hq, cfg.Hkv, cfg.d, cfg.blk, cfg.k) > one
+        one = (one + 255) // 256 * 256
+        for t in range(cfg.steps):
+            qs = [H.query_stream(cfg, seed, l, cfg.steps)[t][1] for l in range(cfg.layers)]
+            for M, groups in ((A, True), (Bm, True)) if t else ((A, False), (Bm, False)):
+                regions = 4 if groups else 2 if dev else 1
+                if M is Bm:
+                    if groups or dev:  # the other one meets the size at its first attention, its slots resolved
+                        for L in M:
+                            L.buffers.attn_ws_bytes = regions * one - 1
+                        with pytest.raises(ss.SparseServeError, match="workspace"):
+                            H.decode_step_groups(M, t, qs) if groups else M[0].step(t, qs[0])
+                    for L in M:
+                        L.buffers.attn_ws_bytes = regions * one
+                if groups:
+                    H.decode_step_groups(M, t, qs)
+                else:
+                    for L, q in zip(M, qs):
+                        L.step(t, q)
+            torch.cuda.synchronize()
+            for a, b in zip(A, Bm):
+                assert torch.equal(a.sel, b.sel)
+                assert float((a.out - b.out).abs().max()) <= 2.0 ** -15 * 12
+    finally:
+        close(pa, A)
+        close(pb, Bm)
+
+
 def test_host_groups_schedule_wait_deadline(ss):
     """With the host resolve, a wait for a selection that passes the deadline
     (ss_set_host_wait_timeout) returns SS_ERR_TIMEOUT before any slot table

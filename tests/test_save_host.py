@@ -6,42 +6,12 @@ and the number of copies: one for a save of less than 4 MiB, whatever the
 number of rows left over from whole blocks, at most sqrt(MiB) beyond."""
 import json
 import math
-import os
-import shutil
-import subprocess
-import sys
 
+import hip_stand_in
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-
-STAND_IN = r"""
-#include <stdlib.h>
-#include <string.h>
-static int copies;
-int stand_in_copies(void) { const int n = copies; copies = 0; return n; }
-int hipMemcpyAsync(void *dst, const void *src, size_t n, int kind, void *stream)
-{
-    (void)kind;
-    (void)stream;
-    memcpy(dst, src, n);
-    ++copies; /* the saver copies under its lock */
-    return 0;
-}
-int hipHostMalloc(void **p, size_t n, unsigned flags) { (void)flags; return (*p = aligned_alloc(4096, (n + 4095) / 4096 * 4096)) ? 0 : 2; }
-int hipHostFree(void *p) { free(p); return 0; }
-int hipEventCreateWithFlags(void **e, unsigned flags) { (void)flags; *e = &copies; return 0; }
-int hipEventDestroy(void *e) { (void)e; return 0; }
-int hipEventRecord(void *e, void *stream) { (void)e; (void)stream; return 0; }
-int hipEventSynchronize(void *e) { (void)e; return 0; }
-"""
-
 CHILD = r"""
-import ctypes, json, sys
-stand_in = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
-import numpy as np
 import oracle
-from paper_2509_24626_amd import binding as ss
 c, D = json.loads(sys.argv[2]), 128
 B, n_new, Hkv, blk, lens = c["B"], c["n_new"], c["Hkv"], c["blk"], np.asarray(c["lens"], np.int32)
 rng = np.random.default_rng(B * 1000 + n_new)
@@ -66,14 +36,7 @@ print(json.dumps({"copies": copies, "equal": bool(np.array_equal(pool, want))}))
 
 @pytest.fixture(scope="module")
 def stand_in(tmp_path_factory):
-    cc = shutil.which("gcc")
-    if cc is None:
-        pytest.skip("no C compiler")
-    d = tmp_path_factory.mktemp("stand_in")
-    (d / "hip.c").write_text(STAND_IN)
-    subprocess.run([cc, "-std=c11", "-O1", "-shared", "-fPIC", "-Wall", "-Werror", str(d / "hip.c"), "-o",
-                    str(d / "hip.so")], check=True)
-    return str(d / "hip.so")
+    return hip_stand_in.build(tmp_path_factory.mktemp("stand_in")) or pytest.skip("no C compiler")
 
 
 @pytest.mark.parametrize("B,n_new,Hkv,blk,lens,threads", [
@@ -92,10 +55,7 @@ def test_copies_and_bytes(stand_in, B, n_new, Hkv, blk, lens, threads):
     size = B * n_new * Hkv * 512
     case = {"B": B, "n_new": n_new, "Hkv": Hkv, "blk": blk, "lens": lens, "threads": threads,
             "saves": 3 if size < (8 << 20) else 1}
-    r = subprocess.run([sys.executable, "-c", CHILD, stand_in, json.dumps(case)], cwd=ROOT, capture_output=True,
-                       text=True, timeout=120)
-    assert r.returncode == 0, r.stdout + r.stderr
-    got = json.loads(r.stdout.splitlines()[-1])
+    got = json.loads(hip_stand_in.run(stand_in, CHILD, json.dumps(case)))
     assert got["equal"]
     most = max(1, int(math.sqrt(size / (1 << 20))))
     assert all(1 <= n <= most for n in got["copies"]), (got["copies"], most)
