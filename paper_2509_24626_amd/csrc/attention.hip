@@ -302,11 +302,14 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
                                                      float *__restrict__ out)
 {
     constexpr int CHUNK = 16;
+    static_assert(kMaxSplits <= 64 && kMaxSplits % CHUNK == 0, "one split per lane, whole chunks of them");
     const int u = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
     const int b = u / Hkv, g = u - b * Hkv;
     const float *p = ws + ((int64_t)u * splits * G + h) * (D + 2);
     const int64_t stride = (int64_t)G * (D + 2);
     f32x2_t x[CHUNK];
+    // past the last split: its partial again, read and then dropped (it may be
+    // infinite, so a weight of 0 would not do)
     auto load = [&](int s0) {
 #pragma unroll
         for (int i = 0; i < CHUNK; ++i)
@@ -315,31 +318,26 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
     f32x2_t ml = {-INFINITY, 0.f};
     if (lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + lane * stride);
     load(0);
-    float M = ml.x;
-    for (int s = lane + 64; s < splits; s += 64) M = fmaxf(M, p[s * stride]);
-    M = wave_max(M);
+    const float M = wave_max(ml.x);
     float lsum = 0.f;
     f32x2_t osum = {0.f, 0.f};
-    if (M != -INFINITY)
-        for (int s0 = 0; s0 < splits; s0 += CHUNK) {
-            const int at = s0 & 63;  // lane of the chunk's first split
-            if (s0 > 0) {
-                load(s0);
-                if (at == 0) {
-                    ml = f32x2_t{-INFINITY, 0.f};
-                    if (s0 + lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + (s0 + lane) * stride);
-                }
-            }
-            const float w = __builtin_amdgcn_exp2f(ml.x - M);  // 0 past the last split
-            const float wl = w * ml.y;
+    if (M != -INFINITY) {
+        const float w = __builtin_amdgcn_exp2f(ml.x - M);  // 0 past the last split
+        const float wl = w * ml.y;
+#pragma unroll
+        for (int s0 = 0; s0 < kMaxSplits; s0 += CHUNK) {
+            if (s0 >= splits) break;
+            if (s0 > 0) load(s0);
 #pragma unroll
             for (int i = 0; i < CHUNK; ++i) {
-                const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), at + i));
-                lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), at + i));
-                osum.x += sc * x[i].x;
-                osum.y += sc * x[i].y;
+                const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s0 + i));
+                const bool in = s0 + i < splits;
+                lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), s0 + i));
+                osum.x += sc * (in ? x[i].x : 0.f);
+                osum.y += sc * (in ? x[i].y : 0.f);
             }
         }
+    }
     f32x2_t y = {0.f, 0.f};
     if (lsum > 0.f) y = f32x2_t{osum.x / lsum, osum.y / lsum};
     *reinterpret_cast<f32x2_t *>(out + ((int64_t)b * Hq + g * G + h) * D + 2 * lane) = y;

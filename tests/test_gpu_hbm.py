@@ -596,6 +596,31 @@ def test_attention_with_less_workspace(ss, units, k, splits):
         assert float((out - got[0]).abs().max()) <= 2.0 ** -15 * float(kv.abs().max())
 
 
+@pytest.mark.parametrize("units,k,limit", [(8, 128, 32), (8, 128, 16), (8, 128, 8), (44, 256, 32), (1, 512, 32)])
+def test_attention_merge_keeps_infinities(ss, units, k, limit):
+    """A channel whose 32-bit sums overflow is infinite in every split's
+    partial, and so is the output: the merge multiplies no partial that it is
+    to leave out (0 * inf is no number).  19 splits, 16, 8, 5 and 32, on
+    either side of the 16 that are read at a time."""
+    G, blk, d = 4, 16, 128
+    g = torch.Generator(device="cuda").manual_seed(units + limit)
+    kv = torch.randn(units, k, 2, blk * d, generator=g, device="cuda").bfloat16()
+    kv[:, :, 1].view(units, k, d, blk)[:, :, 5] = 3e38
+    kv[:, :, 1].view(units, k, d, blk)[:, :, 77] = -3e38
+    q = torch.zeros(units, G, d, device="cuda").bfloat16()  # every probability alike
+    sel = torch.arange(k, dtype=torch.int32, device="cuda").repeat(units, 1)
+    off = torch.arange(units, dtype=torch.int64, device="cuda") * k * 2 * blk * d * 2
+    size = min(ss.ss_sparse_attention_workspace(units, G, 1, d, blk, k), limit * units * G * (d + 2) * 4)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    out = torch.empty(units, G, d, device="cuda")
+    print(f"[gpu] attention with overflowing sums: {units} units, k {k}, at most {limit} splits", flush=True)
+    ss.ss_sparse_attention(q, kv, off, sel, None, k, units, G, 1, d, blk, k, d ** -0.5, out, ws, size)
+    assert bool((out[:, :, 5] == float("inf")).all()) and bool((out[:, :, 77] == float("-inf")).all())
+    rest = torch.ones(d, dtype=torch.bool)
+    rest[[5, 77]] = False
+    assert bool(out[:, :, rest].isfinite().all())
+
+
 @pytest.mark.parametrize("kind,agg", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("nblk,G", [((1, 15, 0), 1), ((16, 17, 31), 4), ((33, 48, 32), 7), ((1000, 40, 999), 16),
                                     ((40000, 65, 39985), 2)])
