@@ -51,13 +51,13 @@ constexpr size_t kStageBytes = (size_t)WAVES * ss::tile_shape<0>::STAGE * 16;
 template <int KIND, int AGG>
 __global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__restrict__ q,
                                                            const uint8_t *__restrict__ meta,
-                                                           const int32_t *__restrict__ nblk, int Hq, int Hkv, int G,
-                                                           int nblk_max, int chunks_per_unit,
+                                                           const int32_t *__restrict__ nblk, int u0, int Hq, int Hkv,
+                                                           int G, int nblk_max, int chunks_per_unit,
                                                            float *__restrict__ scores)
 {
     __shared__ uint4 stage[WAVES][ss::tile_shape<KIND>::STAGE];
-    const int u = blockIdx.x / chunks_per_unit;
-    const int chunk = blockIdx.x - u * chunks_per_unit;
+    const int uc = blockIdx.x / chunks_per_unit;
+    const int u = u0 + uc, chunk = blockIdx.x - uc * chunks_per_unit;
     const int b = u / Hkv, g = u - b * Hkv;
     int n = nblk[b];
     n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
@@ -78,18 +78,25 @@ ss_status launch_score(const void *q, const void *meta, int meta_kind, int agg, 
                        int Hkv, int nblk_max, float *scores, hipStream_t s)
 {
     const int chunks = (nblk_max + BLOCKS_PER_WG - 1) / BLOCKS_PER_WG;
-    const int64_t grid = (int64_t)B * Hkv * chunks;
-    if (grid == 0) return SS_OK;
-    SS_CHECK_SUPPORTED(grid * WAVES * 64 <= 0xFFFFFFFFll, "score: grid too large");
+    const int64_t units = (int64_t)B * Hkv;
+    if (units * chunks == 0) return SS_OK;
+    // what one launch of 256 threads per 256 blocks holds is taken; these
+    // shorter workgroups may need several launches for it
+    SS_CHECK_SUPPORTED(units * ((nblk_max + 255) / 256) <= 0xFFFFFFFFll / 256, "score: grid too large");
+    const int64_t per = 0xFFFFFFFFll / (WAVES * 64) / chunks;  // units per launch
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *mm = static_cast<const uint8_t *>(meta);
-    const dim3 gr((unsigned)grid), bl(WAVES * 64);
+    const dim3 bl(WAVES * 64);
     const int G = Hq / Hkv;
     auto *kernel = score_kernel<0, 0>;
     if (meta_kind == SS_META_CUBOID) kernel = agg == SS_AGG_MAX ? score_kernel<0, 0> : score_kernel<0, 1>;
     else kernel = agg == SS_AGG_MAX ? score_kernel<1, 0> : score_kernel<1, 1>;
-    const bool cap = meta_kind == SS_META_CUBOID && grid > kResident;
-    ss::launch_lds(kernel, gr, bl, cap ? kResidencyLds - kStageBytes : 0, s, qq, mm, nblk, Hq, Hkv, G, nblk_max, chunks, scores);
+    for (int64_t u0 = 0; u0 < units; u0 += per) {
+        const int64_t grid = (units - u0 < per ? units - u0 : per) * chunks;
+        const bool cap = meta_kind == SS_META_CUBOID && grid > kResident;
+        ss::launch_lds(kernel, dim3((unsigned)grid), bl, cap ? kResidencyLds - kStageBytes : 0, s, qq, mm, nblk, (int)u0,
+                       Hq, Hkv, G, nblk_max, chunks, scores);
+    }
     return check_launch("ss_score_blocks");
 }
 

@@ -492,13 +492,16 @@ extern "C" ss_status ss_score_topk(const void *q, const void *meta, const int32_
     // and one: 4 units of 256 blocks 7.5, 5.5; 256 units of 256 10.9, 9.0; 512
     // of 100 10.2, 7.2; 512 of 64 8.6, 5.7.  16 waves fill a CU, so beyond one
     // unit a CU the selections no longer hide under other units' loads (512
-    // units of 256 blocks 15.8, 16.7).
-    if (nblk_max >= 1 && (nblk_max <= 8 * ss::kTile || (nblk_max <= 16 * ss::kTile && B * Hkv <= 256))) {
-        auto *kernel = score_topk_kernel<16>;
-        int waves = 16;
-        if (nblk_max <= 4 * ss::kTile) kernel = score_topk_kernel<4>, waves = 4;
-        else if (nblk_max <= 8 * ss::kTile) kernel = score_topk_kernel<8>, waves = 8;
-        ss::launch(kernel, dim3(B * Hkv), dim3(waves * 64), s, static_cast<const uint16_t *>(q),
+    // units of 256 blocks 15.8, 16.7).  Units that do not fit a launch are left
+    // to the two, which know how far they go.
+    const int64_t units = (int64_t)B * Hkv;
+    auto *kernel = score_topk_kernel<16>;
+    int waves = 16;
+    if (nblk_max <= 4 * ss::kTile) kernel = score_topk_kernel<4>, waves = 4;
+    else if (nblk_max <= 8 * ss::kTile) kernel = score_topk_kernel<8>, waves = 8;
+    if (nblk_max >= 1 && nblk_max <= waves * ss::kTile && (waves < 16 || units <= 256) &&
+        units * waves * 64 <= 0xFFFFFFFFll) {
+        ss::launch(kernel, dim3((unsigned)units), dim3(waves * 64), s, static_cast<const uint16_t *>(q),
                    static_cast<const uint8_t *>(meta), nblk, Hq, Hkv, Hq / Hkv, nblk_max, k, scores, sel);
         return ss::check_launch("ss_score_topk");
     }

@@ -55,3 +55,45 @@ def test_attention_takes_every_workspace_size(stand_in):
         assert c["least"][0][1] <= c["between"][0][1] <= c["full"][0][1], c
         fewer += c["least"][0][1] < c["full"][0][1]
     assert fewer > 10  # the shapes reach plans with more splits than the least size holds
+
+
+SCORE = r"""
+P, got = 0x1000, []
+for B, Hkv, n in json.loads(sys.argv[2]):
+    made = {}
+    for name, call in (("score", lambda: ss.ss_score_blocks(P, P, P, B, Hkv, Hkv, n, 128, P, stream=0)),
+                       ("mean", lambda: ss.ss_score_blocks_variant(P, P, 1, 1, P, B, Hkv, Hkv, n, 128, P, stream=0)),
+                       ("topk", lambda: ss.ss_score_topk(P, P, P, B, Hkv, Hkv, n, 128, 4, P, P, stream=0))):
+        try:
+            call()
+            made[name] = launches()
+        except ss.SparseServeError as e:
+            assert e.status == ss.SS_ERR_UNSUPPORTED and launches() == []
+            made[name] = None
+    got.append(made)
+print(json.dumps(got))
+"""
+
+
+@pytest.mark.parametrize("B,Hkv,n,taken", [
+    (1, 1, 1, True), (64, 8, 8192, True), (512, 8, 128, True),
+    (1 << 19, 8, 256, True), (1, 1 << 22, 256, True),    # 2^22 units of eight score workgroups: more than one launch
+    (1 << 20, 8, 100, True), (3, 1 << 21, 129, True),
+    ((1 << 21) - 1, 8, 16, True),
+    (1 << 20, 1 << 12, 16, False), (1 << 21, 8, 16, False), (1 << 12, 1 << 20, 128, False),  # 2^32, 2^24 units
+    (1 << 15, 8, 65536, False)])
+def test_score_launch_limits(stand_in, B, Hkv, n, taken):
+    """Scoring takes up to 2^32 - 1 threads' worth of 256-block pieces, as it
+    always has, in as many launches as the smaller pieces of today need, none
+    of them past the 2^32 - 1 threads of a launch; more is refused, by
+    ss_score_topk for short rows too."""
+    made = json.loads(hip_stand_in.run(stand_in, SCORE, json.dumps([(B, Hkv, n)])))[0]
+    units = B * Hkv
+    for name, shapes in made.items():
+        assert (shapes is not None) == taken, (name, shapes)
+        if taken:
+            assert all(0 < x * threads < 1 << 32 for x, _, _, threads in shapes), (name, shapes)
+            if name != "topk":
+                assert sum(x for x, _, _, _ in shapes) == units * (-(-n // 32)), (name, shapes)
+            else:
+                assert shapes[-1][0] == units, shapes
