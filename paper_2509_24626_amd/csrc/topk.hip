@@ -17,8 +17,10 @@
 //     (a shift of key - lowest key) and counted into them in LDS; the interval
 //     of the m-th largest key holds few of them (about ten of 8192 Gaussian
 //     scores with k = 128).  They are collected in LDS, and every wave finds
-//     the bound among them by itself, bit by bit.  An interval with too many
-//     keys is cut again.
+//     the bound among them by itself, bit by bit, one key a lane.  An interval
+//     with more keys than lanes is cut again: searched in place, up to 512 of
+//     them eight a lane, few distinct values cost every wave all their bits
+//     (1024 units of 1025 whole numbers below 200: 15.9 us, cut again 9.8).
 // LDS atomics of one instruction to one address are done one lane at a time,
 // so the counts go to 8 copies (lane l to copy l mod 8), laid out so that the
 // copies of an interval lie in different banks and four intervals of a copy
@@ -34,7 +36,8 @@
 // 8 units of 8192 blocks 9.4, 5.7; 512 units 12.1, 7.9; 256 of 2048 6.0, 4.4;
 // 192 of 16384 (k = 512) 13.0, 10.6; 8 of 65536 55.8, 21.7.  Outliers above a
 // tight band, 512 units of 8192: 19.9, 12.6; one value but for one: 52.5,
-// 14.4; 200 distinct values, 256 of 2048: 6.6, 7.7.
+// 14.4.  In graphs: whole numbers below 200, 1024 units of 1025 10.9, 9.7; N(0,1),
+// 512 of 1025 7.4, 6.1.
 #include <climits>
 
 #include "score_tile.hpp"
@@ -43,8 +46,7 @@ namespace {
 
 constexpr int kCopies = 8;            // copies of the interval counts
 constexpr int kPitch = 256 + 4;        // words per copy: one interval's copies lie in different banks
-constexpr int kCandRegs = 8;           // keys per lane of the last search
-constexpr int kCand = 64 * kCandRegs;  // most keys it takes
+constexpr int kCand = 64;              // most keys of the last search, one per lane
 constexpr int kBufferFlags = 0x00020000;  // raw buffer descriptor word 3 for gfx9 (32-bit data)
 
 // order-preserving key of a score's bits; at least 1 (0 is padding)
@@ -219,10 +221,12 @@ __device__ __forceinline__ void place(const uint32_t (&key)[R], bound_t bound, i
         }
 }
 
+// R = 16 is held to the 64 registers at which two workgroups of 1024 threads share a CU
 template <int NT, int R>
-__global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scores, const int32_t *__restrict__ nblk,
-                                                  int Hkv, int nblk_max, int k, int32_t *__restrict__ sel,
-                                                  int32_t *__restrict__ mirror)
+__global__ __launch_bounds__(NT, R == 16 ? 8 : 1) void topk_kernel(const float *__restrict__ scores,
+                                                                   const int32_t *__restrict__ nblk, int Hkv,
+                                                                   int nblk_max, int k, int32_t *__restrict__ sel,
+                                                                   int32_t *__restrict__ mirror)
 {
     constexpr int NW = NT / 64;
     const int u = blockIdx.x;
@@ -354,15 +358,8 @@ __global__ __launch_bounds__(NT) void topk_kernel(const float *__restrict__ scor
                         }
                     }
                     __syncthreads();
-                    if (held <= 64) {
-                        const uint32_t off[1] = {lane < held ? cand[lane] : 0u};
-                        bound = search(off, lo, span, want);
-                    } else {
-                        uint32_t off[kCandRegs];
-#pragma unroll
-                        for (int i = 0; i < kCandRegs; ++i) off[i] = i * 64 + lane < held ? cand[i * 64 + lane] : 0u;
-                        bound = search(off, lo, span, want);
-                    }
+                    const uint32_t off[1] = {lane < held ? cand[lane] : 0u};
+                    bound = search(off, lo, span, want);
                     break;
                 }
                 if (span) {

@@ -530,6 +530,38 @@ def test_topk_launch_shapes_and_extremes(ss, oracle_impl, n):
         np.testing.assert_array_equal(sel.cpu().numpy(), ref, err_msg=f"n={n} k={k}")
 
 
+@pytest.mark.parametrize("n", [300, 1000, 2048, 5000, 16384])
+def test_topk_clusters_at_the_bound(ss, oracle_impl, n):
+    """Clusters of scores around the bound of just fewer, as many and more
+    than the last search takes (64), of distinct, of few and of equal values,
+    inside a range so wide that one interval holds them all; whole numbers on
+    either side of zero, and scores that are mostly zero.  Equal to the
+    oracle's selection."""
+    rng = np.random.default_rng(n)
+    sizes = [63, 64, 65, 129, 280]
+    rows, ks = [], []
+    for c in sizes:
+        for kind in range(3):
+            x = np.full(n, -1e30, np.float32)
+            at = rng.permutation(n)
+            x[at[:10]] = 1e30
+            near = 1 + np.arange(c) * np.float32(2.0 ** -22)
+            x[at[10:10 + c]] = near if kind == 0 else near[rng.integers(0, 3, c)] if kind == 1 else near[0]
+            rows.append(x)
+            ks.append(10 + c // 2)
+    for x in ((50 * rng.standard_normal(n)).round(), rng.integers(0, 200, n), np.maximum(rng.standard_normal(n), 0),
+              rng.standard_normal(n), rng.integers(0, 3, n)):
+        rows.append(x.astype(np.float32))
+        ks.append(128)
+    sc = np.stack(rows)[:, None]
+    nblk = np.full(len(rows), n, np.int32)
+    for k in sorted(set(ks) | {100}):
+        sel = torch.empty(len(rows), 1, k, dtype=torch.int32, device="cuda")
+        ss.ss_select_topk(torch.from_numpy(sc).cuda(), torch.from_numpy(nblk).cuda(), len(rows), 1, n, k, sel)
+        ref = oracle_impl.select(sc.astype(np.float64), nblk, k)
+        np.testing.assert_array_equal(sel.cpu().numpy(), ref, err_msg=f"n={n} k={k}")
+
+
 @pytest.mark.parametrize("units,G,blk,k", [(1, 16, 8, 1), (3, 4, 16, 15), (3, 4, 16, 31), (2, 7, 16, 32), (5, 7, 8, 65),
                                            (1, 5, 16, 700), (95, 4, 16, 96), (96, 4, 16, 97), (96, 1, 32, 48),
                                            (143, 4, 16, 40), (144, 4, 16, 40), (256, 2, 8, 33), (257, 2, 16, 40),
