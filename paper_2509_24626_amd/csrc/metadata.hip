@@ -3,8 +3,8 @@
 // or, as the mean-key variant, the mean of the block's keys.
 //
 // HBM bounds it: each key is read once, and little is written.  A wave owns
-// up to 8 consecutive blocks of one unit and issues all of its loads (16 KiB
-// for cuboids) before it reduces anything.  Keys that cannot still lie in the
+// up to 8 consecutive blocks and issues all of its loads (16 KiB for cuboids)
+// before it reduces anything.  Keys that cannot still lie in the
 // 256 MB last-level cache (more than kLargeBytes of them) are read with the
 // non-temporal policy, and with the heads' waves side by side where the
 // heads' rows are interleaved (place(), below).  A layer of a 128k-token
@@ -61,8 +61,8 @@ __device__ __forceinline__ T load(const T *p)
 }
 
 struct place_t {
-    int64_t u;  // unit
-    int j0, n;  // first block of the wave, blocks of the unit
+    uint32_t u;  // unit
+    int j0, n;   // first block of the wave, blocks of the unit
 };
 
 // Wave -> `per` consecutive blocks of a unit.  Where a unit's keys lie on
@@ -71,23 +71,27 @@ struct place_t {
 // heads of the same blocks, so that together they read whole tokens: one head
 // at a time, all reads in flight fall on the same 256 bytes of every token,
 // which are few of the memory channels.
-__device__ __forceinline__ place_t place(int64_t wave, int per, const int32_t *nblk, int Hkv, int nblk_max,
-                                         int heads_inner)
+// A launch has fewer than 2^26 waves, so I may be 32 bits wide (the cuboid of
+// one block of 16 takes 2.45 us with them and 2.56 with 64; but the mean keys
+// of a large token-major prompt in blocks of 8 53.0 us with them, 50.9 with 64).
+template <class I>
+__device__ __forceinline__ place_t place(I wave, int per, const int32_t *nblk, int Hkv, int nblk_max, int heads_inner)
 {
     const int groups = (nblk_max + per - 1) / per;
     place_t p;
-    int64_t grp;
+    I grp;
     if (heads_inner) {
-        const int64_t x = wave / Hkv;
-        const int64_t b = x / groups;
-        p.u = b * Hkv + (wave - x * Hkv);
+        const I x = wave / Hkv;
+        const I b = x / groups;
+        p.u = (uint32_t)(b * Hkv + (wave - x * Hkv));
         grp = x - b * groups;
     } else {
-        p.u = wave / groups;
-        grp = wave - p.u * groups;
+        const I u = wave / groups;
+        p.u = (uint32_t)u;
+        grp = wave - u * groups;
     }
     p.j0 = (int)grp * per;
-    const int n = nblk[p.u / Hkv];
+    const int n = nblk[(I)p.u / Hkv];
     p.n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
     return p;
 }
@@ -98,31 +102,10 @@ __device__ __forceinline__ place_t place(int64_t wave, int per, const int32_t *n
 // four blocks, lane row r ends with block r of them.  The largest key is
 // found as the complement of the smallest complement, so every step is one
 // packed minimum.
-template <int BLK, bool STREAM>
-__global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restrict__ kv_base,
-                                                          const int64_t *__restrict__ unit_off,
-                                                          const int32_t *__restrict__ nblk, int Hkv, int nblk_max,
-                                                          int64_t waves, int heads_inner, int64_t block_stride,
-                                                          int64_t row_stride, uint16_t *__restrict__ meta)
+// The wave's blocks from their loaded rows to m; live(b): block b is stored.
+template <int BPW, int LPB, class Live>
+__device__ __forceinline__ void reduce_blocks(const u32x4_t (&v)[BPW][LPB], uint16_t *m, int row, const Live &live)
 {
-    constexpr int BPW = 64 / BLK;  // blocks per wave: 16 loads of 16 B per lane in flight
-    constexpr int LPB = BLK / 4;   // wave-wide loads per K tile (4 rows each)
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= waves) return;
-    const place_t p = place(w, BPW, nblk, Hkv, nblk_max, heads_inner);
-    if (p.j0 >= p.n) return;
-    const int row = lane >> 4, c16 = lane & 15;
-    const uint8_t *src = kv_base + unit_off[p.u] + row * row_stride + c16 * 16;
-
-    u32x4_t v[BPW][LPB];
-#pragma unroll
-    for (int b = 0; b < BPW; ++b) {
-        const int j = min(p.j0 + b, p.n - 1);  // past the end: the last block again, not stored
-#pragma unroll
-        for (int r = 0; r < LPB; ++r)
-            v[b][r] = load<STREAM>(reinterpret_cast<const u32x4_t *>(src + j * block_stride + 4 * r * row_stride));
-    }
     uint32_t lo[BPW][4], nhi[BPW][4];  // nhi: complements of the largest keys
 #pragma unroll
     for (int b = 0; b < BPW; ++b)
@@ -137,7 +120,6 @@ __global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restr
                 nhi[b][i] = min2(nhi[b][i], ~k);
             }
         }
-    uint16_t *m = meta + (p.u * nblk_max + p.j0) * (2 * D) + c16 * 8;
     if constexpr (BPW == 2) {
         // lane rows 0, 1: lo and hi of the first block, rows 2, 3: of the second
         uint4 x;
@@ -147,7 +129,7 @@ __global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restr
             const uint32_t k = min_rows(min_halves(lo[0][i], lo[1][i]), min_halves(nhi[0][i], nhi[1][i]));
             xs[i] = key2(row & 1 ? ~k : k);
         }
-        if (p.j0 + (row >> 1) < p.n) *reinterpret_cast<uint4 *>(m + row * D) = x;
+        if (live(row >> 1)) *reinterpret_cast<uint4 *>(m + row * D) = x;
     } else {
 #pragma unroll
         for (int b = 0; b < BPW; b += 4) {
@@ -159,12 +141,103 @@ __global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restr
                 ys[i] = key2(~min_rows(min_halves(nhi[b][i], nhi[b + 2][i]),
                                        min_halves(nhi[b + 1][i], nhi[b + 3][i])));
             }
-            if (p.j0 + b + row < p.n) {
+            if (live(b + row)) {
                 *reinterpret_cast<uint4 *>(m + (b + row) * (2 * D)) = x;
                 *reinterpret_cast<uint4 *>(m + (b + row) * (2 * D) + D) = y;
             }
         }
     }
+}
+
+template <int BLK, bool STREAM>
+__global__ __launch_bounds__(WAVES * 64) void meta_kernel(const uint8_t *__restrict__ kv_base,
+                                                          const int64_t *__restrict__ unit_off,
+                                                          const int32_t *__restrict__ nblk, int Hkv, int nblk_max,
+                                                          uint32_t waves, int heads_inner, int64_t block_stride,
+                                                          int64_t row_stride, uint16_t *__restrict__ meta)
+{
+    constexpr int BPW = 64 / BLK;  // blocks per wave: 16 loads of 16 B per lane in flight
+    constexpr int LPB = BLK / 4;   // wave-wide loads per K tile (4 rows each)
+    const int lane = threadIdx.x & 63;
+    const uint32_t w = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= waves) return;
+    const place_t p = place(w, BPW, nblk, Hkv, nblk_max, heads_inner);
+    if (p.j0 >= p.n) return;
+    const int row = lane >> 4, c16 = lane & 15;
+    const uint8_t *src = kv_base + unit_off[p.u] + row * row_stride + c16 * 16;
+
+    u32x4_t v[BPW][LPB];
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+        const int j = min(p.j0 + b, p.n - 1);  // past the end: the last block again, not stored
+#pragma unroll
+        for (int r = 0; r < LPB; ++r)
+            v[b][r] = load<STREAM>(reinterpret_cast<const u32x4_t *>(src + j * block_stride + 4 * r * row_stride));
+    }
+    reduce_blocks(v, meta + ((int64_t)p.u * nblk_max + p.j0) * (2 * D) + c16 * 8, row,
+                  [&](int b) { return p.j0 + b < p.n; });
+}
+
+// The same with a wave's blocks consecutive ones of all units (a unit's last
+// and the next one's first share a wave), whose metadata is consecutive too;
+// missing ones are not read.  Short rows leave no part of a wave idle that way,
+// and more of a large launch's loads are in flight; where a launch is small the
+// look-up of each block's unit costs 0.3 to 1 us.  us, units of n blocks: a wave
+// per unit's blocks before and now, and this (keys read once, four sets in turn):
+// 16384 x 1 in blocks of 8 17.7, 17.7, 9.7; 65536 x 1 in blocks of 32 172, 172,
+// 98; 8192 x 33 of 8 146, 146, 128; 512 x 9 of 8 4.4, 4.4, 5.0.
+template <int BLK, bool STREAM>
+__global__ __launch_bounds__(WAVES * 64) void meta_flat_kernel(const uint8_t *__restrict__ kv_base,
+                                                               const int64_t *__restrict__ unit_off,
+                                                               const int32_t *__restrict__ nblk, uint32_t units,
+                                                               int Hkv, int nblk_max, uint32_t waves,
+                                                               int64_t block_stride, int64_t row_stride,
+                                                               uint16_t *__restrict__ meta)
+{
+    constexpr int BPW = 64 / BLK;
+    constexpr int LPB = BLK / 4;
+    const int lane = threadIdx.x & 63;
+    const uint32_t w = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= waves) return;
+    const int row = lane >> 4, c16 = lane & 15;
+    // where the blocks lie, then all units' counts and offsets side by side
+    uint32_t u = w * BPW / (uint32_t)nblk_max, seq = u / (uint32_t)Hkv;
+    int j = (int)(w * BPW - u * nblk_max), g = (int)(u - seq * Hkv);
+    const uint32_t last = units - 1, last_seq = last / (uint32_t)Hkv;
+    int n[BPW], at[BPW];
+    int64_t off[BPW];
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+        at[b] = u < units ? j : nblk_max;
+        n[b] = nblk[min(seq, last_seq)];
+        off[b] = unit_off[min(u, last)];
+        if (++j == nblk_max) {
+            j = 0;
+            ++u;
+            if (++g == Hkv) {
+                g = 0;
+                ++seq;
+            }
+        }
+    }
+    uint32_t live = 0;
+    u32x4_t v[BPW][LPB];
+    const uint8_t *base = kv_base + row * row_stride + c16 * 16;
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+        if (at[b] < min(n[b], nblk_max)) {
+            live |= 1u << b;
+            const uint8_t *src = base + off[b] + at[b] * block_stride;
+#pragma unroll
+            for (int r = 0; r < LPB; ++r)
+                v[b][r] = load<STREAM>(reinterpret_cast<const u32x4_t *>(src + 4 * r * row_stride));
+        } else {
+#pragma unroll
+            for (int r = 0; r < LPB; ++r) v[b][r] = u32x4_t{0, 0, 0, 0};
+        }
+    }
+    if (!live) return;
+    reduce_blocks(v, meta + (int64_t)w * BPW * (2 * D) + c16 * 8, row, [&](int b) { return (live >> b & 1u) != 0; });
 }
 
 // Mean key of each block: one wave per block, each lane two channels (with
@@ -177,14 +250,14 @@ template <int BLK, bool STREAM>
 __global__ __launch_bounds__(WAVES * 64) void meta_mean_kernel(const uint8_t *__restrict__ kv_base,
                                                                const int64_t *__restrict__ unit_off,
                                                                const int32_t *__restrict__ nblk, int Hkv,
-                                                               int nblk_max, int64_t waves, int heads_inner,
+                                                               int nblk_max, uint32_t waves, int heads_inner,
                                                                int64_t block_stride, int64_t row_stride,
                                                                uint16_t *__restrict__ meta)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t w = blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w >= waves) return;
-    const place_t p = place(w, 1, nblk, Hkv, nblk_max, heads_inner);
+    const place_t p = place((int64_t)w, 1, nblk, Hkv, nblk_max, heads_inner);
     if (p.j0 >= p.n) return;
     const uint8_t *src = kv_base + unit_off[p.u] + p.j0 * block_stride + lane * 4;
 
@@ -197,28 +270,23 @@ __global__ __launch_bounds__(WAVES * 64) void meta_mean_kernel(const uint8_t *__
         s0 += (double)__uint_as_float(v[t] << 16);
         s1 += (double)__uint_as_float(v[t] & 0xFFFF0000u);
     }
-    reinterpret_cast<uint32_t *>(meta + (p.u * nblk_max + p.j0) * D)[lane] =
+    reinterpret_cast<uint32_t *>(meta + ((int64_t)p.u * nblk_max + p.j0) * D)[lane] =
         ss::pack_bf16_rne_f64(s0 * (1.0 / BLK), s1 * (1.0 / BLK));
 }
 
-template <bool STREAM>
-void launch_metadata(int meta_kind, int blk, dim3 gr, dim3 bl, hipStream_t s, const uint8_t *kv,
-                     const int64_t *unit_off, const int32_t *nblk, int Hkv, int nblk_max, int64_t waves, int inner,
-                     int64_t bs, int64_t rs, uint16_t *m)
+// the kernel for a kind, a block size and a cache policy; flat: cuboids in meta_flat_kernel
+template <int BLK, bool STREAM>
+void launch_blk(int meta_kind, bool flat, dim3 gr, hipStream_t s, const uint8_t *kv, const int64_t *unit_off,
+                const int32_t *nblk, int64_t units, int Hkv, int nblk_max, int64_t waves, int inner, int64_t bs,
+                int64_t rs, uint16_t *m)
 {
-    if (meta_kind == SS_META_CUBOID) {
-        switch (blk) {
-        case 8: ss::launch(meta_kernel<8, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        case 16: ss::launch(meta_kernel<16, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        default: ss::launch(meta_kernel<32, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        }
-    } else {
-        switch (blk) {
-        case 8: ss::launch(meta_mean_kernel<8, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        case 16: ss::launch(meta_mean_kernel<16, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        default: ss::launch(meta_mean_kernel<32, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m); break;
-        }
-    }
+    const dim3 bl(WAVES * 64);
+    if (flat)
+        ss::launch(meta_flat_kernel<BLK, STREAM>, gr, bl, s, kv, unit_off, nblk, units, Hkv, nblk_max, waves, bs, rs, m);
+    else if (meta_kind == SS_META_CUBOID)
+        ss::launch(meta_kernel<BLK, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m);
+    else
+        ss::launch(meta_mean_kernel<BLK, STREAM>, gr, bl, s, kv, unit_off, nblk, Hkv, nblk_max, waves, inner, bs, rs, m);
 }
 
 }  // namespace
@@ -242,18 +310,33 @@ extern "C" ss_status ss_build_metadata_strided(const void *kv_base, const int64_
     SS_CHECK_ARG(((uintptr_t)kv_base & 15) == 0 && ((uintptr_t)meta & 15) == 0,
                  "ss_build_metadata: kv_base and meta must be 16-byte aligned");
     const int per = meta_kind == SS_META_CUBOID ? 64 / blk : 1;  // blocks per wave
-    const int64_t waves = (int64_t)B * Hkv * ((nblk_max + per - 1) / per);
-    const int64_t grid = (waves + WAVES - 1) / WAVES;
-    SS_CHECK_SUPPORTED(grid <= 0x7FFFFFFF, "ss_build_metadata: too many blocks");
+    const int64_t units = (int64_t)B * Hkv, rows = units * nblk_max * blk;
+    const int64_t flat_waves = (units * nblk_max + per - 1) / per;
+    const int64_t grid_least = (flat_waves + WAVES - 1) / WAVES;
+    SS_CHECK_SUPPORTED(grid_least * WAVES * 64 <= 0xFFFFFFFFll, "ss_build_metadata: too many blocks");
+    const bool large = rows * (d * 2) > kLargeBytes;
+    const int64_t unit_waves = units * ((nblk_max + per - 1) / per);
+    // Other heads' rows lie between a head's rows.  In rows of 16 waves or more
+    // the last one of each, which may hold one block, is lost among them.
+    const int inner = large && row_stride > d * 2 && nblk_max >= 16 * per && unit_waves * 64 <= 0xFFFFFFFFll;
+    // From 64 MiB of keys on the blocks go to waves across the units (64 MiB in
+    // blocks of 8, 2048 units: 16.6 us both ways, 128 MiB 40.3 and 37.6, 256 MiB
+    // 73.1 and 64.6; 8 MiB, 256 units, 6.1 and 7.7); so do many units that would
+    // fill half a wave each (4096 of one block of 8: 6.4 and 4.9 us, of 16 7.1 and
+    // 5.7; 2048: 3.9 and 4.6, 4.4 and 4.2).
+    // Rows with others between them gain nothing before they come from HBM
+    // (1024 blocks of 32, 8 heads, token-major: 36.8 and 38.8 us).
+    const bool flat = meta_kind == SS_META_CUBOID && !inner &&
+                      ((row_stride > d * 2 ? large : rows > (1 << 18)) || (units >= 4096 && 2 * nblk_max <= per));
+    const int64_t waves = flat ? flat_waves : unit_waves;
     hipStream_t s = ss::as_stream(stream);
     const uint8_t *kv = static_cast<const uint8_t *>(kv_base);
-    const dim3 gr((unsigned)grid), bl(WAVES * 64);
-    const int64_t bs = block_stride, rs = row_stride;
-    const bool large = (int64_t)B * Hkv * nblk_max * blk * (d * 2) > kLargeBytes;
-    const int inner = large && row_stride > d * 2;  // other heads' rows lie between a head's rows
-    uint16_t *m = static_cast<uint16_t *>(meta);
-    (large ? launch_metadata<true> : launch_metadata<false>)(meta_kind, blk, gr, bl, s, kv, unit_off, nblk, Hkv,
-                                                             nblk_max, waves, inner, bs, rs, m);
+    const dim3 gr((unsigned)((waves + WAVES - 1) / WAVES));
+    auto *go = large ? launch_blk<32, true> : launch_blk<32, false>;
+    if (blk == 8) go = large ? launch_blk<8, true> : launch_blk<8, false>;
+    else if (blk == 16) go = large ? launch_blk<16, true> : launch_blk<16, false>;
+    go(meta_kind, flat, gr, s, kv, unit_off, nblk, units, Hkv, nblk_max, waves, inner, block_stride, row_stride,
+       static_cast<uint16_t *>(meta));
     return ss::check_launch("ss_build_metadata");
 }
 

@@ -97,3 +97,36 @@ def test_score_launch_limits(stand_in, B, Hkv, n, taken):
                 assert sum(x for x, _, _, _ in shapes) == units * (-(-n // 32)), (name, shapes)
             else:
                 assert shapes[-1][0] == units, shapes
+
+
+METADATA = r"""
+P, got = 0x1000, []
+for B, Hkv, n, blk, row in json.loads(sys.argv[2]):
+    made = []
+    for kind in (0, 1):
+        try:
+            ss.ss_build_metadata_strided(P, P, P, B, Hkv, n, blk, 128, blk * row, row, kind, P, stream=0)
+            made.append(launches())
+        except ss.SparseServeError as e:
+            assert e.status == ss.SS_ERR_UNSUPPORTED and launches() == []
+            made.append(None)
+    got.append(made)
+print(json.dumps(got))
+"""
+
+
+@pytest.mark.parametrize("B,Hkv,n,blk,row,cuboid,mean", [
+    (1, 1, 1, 8, 256, True, True), (1, 8, 8192, 16, 4096, True, True),
+    (1 << 25, 8, 1, 8, 256, True, False),                # 2^28 blocks of 8: eight of them a wave, whatever the units
+    (1 << 22, 8, 3, 16, 256, True, False), (1 << 22, 8, 1, 32, 256, True, True),
+    (1 << 13, 8, 65, 8, 4096, True, True), (1 << 20, 8, 61, 8, 4096, True, False),
+    ((1 << 29) - 32, 1, 1, 8, 256, True, False), (1 << 29, 1, 1, 8, 256, False, False)])
+def test_metadata_launch_limits(stand_in, B, Hkv, n, blk, row, cuboid, mean):
+    """Metadata takes what 2^32 - 1 threads of 64/blk blocks (mean keys: one)
+    a wave hold, however short the units' rows are, in one launch."""
+    made = json.loads(hip_stand_in.run(stand_in, METADATA, json.dumps([(B, Hkv, n, blk, row)])))[0]
+    for shapes, taken in zip(made, (cuboid, mean)):
+        assert (shapes is not None) == taken, shapes
+        if taken:
+            (x, _, _, threads), = shapes
+            assert 0 < x * threads < 1 << 32

@@ -500,6 +500,43 @@ def test_metadata_launch_shapes(ss, kind, blk, Hkv, tokens, token_major):
         assert bool((meta[b, :, m:] == 0x7ABC).all())
 
 
+@pytest.mark.parametrize("blk,Hkv,B,n,token_major", [
+    (8, 8, 513, 4, False), (8, 3, 1400, 1, False), (16, 1, 4096, 2, True), (32, 8, 512, 1, False),  # half a wave a unit
+    (8, 8, 512, 4, False), (8, 5, 819, 1, True), (16, 8, 511, 2, False),                              # just fewer units
+    (8, 7, 67, 70, False), (16, 8, 700, 3, False), (32, 2, 1400, 3, False), (8, 8, 1, 4097, False),   # by size
+    (8, 8, 2100, 5, True), (32, 3, 1400, 5, True)])                                                # and by size past the cache
+def test_metadata_rows_across_units(ss, blk, Hkv, B, n, token_major):
+    """Many units of few blocks, whose blocks share waves, on either side of
+    the lines from which they do: counts of 0 to n in turn, so that units
+    begin, end and are missing anywhere in a wave, also in the last one.
+    Bit-exact against min/max over totalOrder keys; the rows past a count
+    keep what they held."""
+    d = 128
+    nblk = torch.tensor([(3 * b + b // 7) % (n + 1) for b in range(B)], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(blk * 10000 + B)
+    shape = (B, n * blk, Hkv, 2, d) if token_major else (B, Hkv, n, 2, blk, d)
+    kv = torch.randn(shape, generator=g, device="cuda").bfloat16()
+    kv.view(-1)[::97] = -0.0
+    if token_major:
+        row, step = Hkv * 2 * d * 2, blk * Hkv * 2 * d * 2
+        off = [b * n * step + h * 2 * d * 2 for b in range(B) for h in range(Hkv)]
+        keys = kv[:, :, :, 0].unflatten(1, (n, blk)).permute(0, 3, 1, 2, 4)
+    else:
+        row, step = d * 2, blk * 2 * d * 2
+        off = [u * n * step for u in range(B * Hkv)]
+        keys = kv[:, :, :, 0]
+    off = torch.tensor(off, dtype=torch.int64, device="cuda")
+    meta = torch.full((B, Hkv, n, 2, d), 0x7ABC, dtype=torch.int16, device="cuda")
+    print(f"[gpu] metadata of {B} x {Hkv} units of {n} blocks of {blk}, token-major {token_major}", flush=True)
+    ss.ss_build_metadata_strided(kv, off, nblk, B, Hkv, n, blk, d, step, row, 0, meta)
+    bits = keys.contiguous().view(torch.int16)
+    order = torch.where(bits < 0, bits ^ 0x7FFF, bits)  # totalOrder as signed integers
+    want = torch.stack([torch.where(x < 0, x ^ 0x7FFF, x) for x in (order.amin(3), order.amax(3))], 3)
+    live = torch.arange(n, device="cuda")[None] < nblk[:, None]
+    want = torch.where(live[:, None, :, None, None], want, torch.full_like(want, 0x7ABC))
+    assert torch.equal(meta, want)
+
+
 @pytest.mark.parametrize("n", [1, 2, 63, 65, 256, 257, 512, 513, 1024, 1025, 2049, 4097, 8193, 16385, 65536])
 def test_topk_launch_shapes_and_extremes(ss, oracle_impl, n):
     """Either side of the launch shapes' row lengths, rows one score short of
