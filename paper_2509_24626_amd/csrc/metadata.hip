@@ -316,9 +316,13 @@ extern "C" ss_status ss_build_metadata_strided(const void *kv_base, const int64_
     SS_CHECK_SUPPORTED(grid_least * WAVES * 64 <= 0xFFFFFFFFll, "ss_build_metadata: too many blocks");
     const bool large = rows * (d * 2) > kLargeBytes;
     const int64_t unit_waves = units * ((nblk_max + per - 1) / per);
-    // Other heads' rows lie between a head's rows.  In rows of 16 waves or more
-    // the last one of each, which may hold one block, is lost among them.
-    const int inner = large && row_stride > d * 2 && nblk_max >= 16 * per && unit_waves * 64 <= 0xFFFFFFFFll;
+    // Other heads' rows lie between a head's rows: the stride spans the keys of
+    // all heads (with two heads it may span their own values instead, which
+    // costs nothing).  Heads that lie one after another, each with its values,
+    // are slower side by side: mean keys of 4 x 16384 blocks of 16 46.4 us, 50.2
+    // that way, cuboids 52.9 and 55.2.  In rows of 16 waves or more the last one
+    // of each, which may hold one block, is lost among them.
+    const int inner = large && Hkv > 1 && row_stride >= (int64_t)Hkv * d * 2 && nblk_max >= 16 * per && unit_waves * 64 <= 0xFFFFFFFFll;
     // From 64 MiB of keys on the blocks go to waves across the units (64 MiB in
     // blocks of 8, 2048 units: 16.6 us both ways, 128 MiB 40.3 and 37.6, 256 MiB
     // 73.1 and 64.6; 8 MiB, 256 units, 6.1 and 7.7); so do many units that would

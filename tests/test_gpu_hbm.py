@@ -537,6 +537,41 @@ def test_metadata_rows_across_units(ss, blk, Hkv, B, n, token_major):
     assert torch.equal(meta, want)
 
 
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("blk,Hkv,n,values", [(16, 4, 10300, True), (8, 2, 41100, True), (16, 1, 41000, True),
+                                              (32, 2, 10300, False), (16, 3, 800, True)])
+def test_metadata_heads_one_after_another(ss, kind, blk, Hkv, n, values):
+    """Keys whose heads lie one after another, [head][token][K, V][d] or, for
+    two heads, keys alone with the heads side by side (the same stride): on
+    either side of the line to keys that come from HBM, with the heads'
+    waves in either order.  Bit-exact as above."""
+    d = 128
+    g = torch.Generator(device="cuda").manual_seed(n + Hkv)
+    if values:
+        kv = torch.randn(Hkv, n, blk, 2, d, generator=g, device="cuda").bfloat16()
+        keys, row = kv[:, :, :, 0], 2 * d * 2
+        off = [h * n * blk * row for h in range(Hkv)]
+    else:
+        kv = torch.randn(n, blk, Hkv, d, generator=g, device="cuda").bfloat16()
+        keys, row = kv.permute(2, 0, 1, 3), Hkv * d * 2
+        off = [h * d * 2 for h in range(Hkv)]
+    off = torch.tensor(off, dtype=torch.int64, device="cuda")
+    nblk = torch.tensor([n - 3], dtype=torch.int32, device="cuda")
+    meta = torch.full((Hkv, n) + ((2, d) if kind == 0 else (d,)), 0x7ABC, dtype=torch.int16, device="cuda")
+    print(f"[gpu] metadata kind {kind}, {Hkv} heads of {n} blocks of {blk}, values between {values}", flush=True)
+    ss.ss_build_metadata_strided(kv, off, nblk, 1, Hkv, n, blk, d, blk * row, row, kind, meta)
+    k = keys.contiguous()
+    if kind == 0:
+        bits = k.view(torch.int16)
+        order = torch.where(bits < 0, bits ^ 0x7FFF, bits)
+        want = torch.stack([torch.where(x < 0, x ^ 0x7FFF, x) for x in (order.amin(2), order.amax(2))], 2)
+    else:
+        x = (k.double().sum(2) / blk).view(torch.int64)
+        x = ((x + ((1 << 44) - 1) + ((x >> 45) & 1)) >> 45) << 45
+        want = x.view(torch.float64).bfloat16().view(torch.int16)
+    assert torch.equal(meta[:, :n - 3], want[:, :n - 3]) and bool((meta[:, n - 3:] == 0x7ABC).all())
+
+
 @pytest.mark.parametrize("n", [1, 2, 63, 65, 256, 257, 512, 513, 1024, 1025, 2049, 4097, 8193, 16385, 65536])
 def test_topk_launch_shapes_and_extremes(ss, oracle_impl, n):
     """Either side of the launch shapes' row lengths, rows one score short of
