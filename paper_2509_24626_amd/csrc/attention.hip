@@ -292,32 +292,29 @@ __device__ __forceinline__ float wave_max(float x)
     return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
 }
 
-// One wave per (unit, head), two channels per lane.  The splits' maxima and
-// sums are read side by side, one split per lane, together with the first
-// partials (none of the loads waits for another), and the weights go round as
-// scalars.  Latency bounds it: 8 splits of 32 heads took 3.3 us with each
-// thread walking the splits twice, 2.5 now; 12 splits of 308 heads 6.4 and 4.6
-// (of which about 2 are the launch).
+// One wave per (unit, head), two channels per lane, at most N splits.  The
+// splits' maxima and sums are read side by side, one split per lane, together
+// with the partials (none of the loads waits for another), and the weights go
+// round as scalars.  Latency bounds it: 8 splits of 32 heads took 3.3 us with
+// each thread walking the splits twice, 2.5 now; 12 splits of 308 heads 6.4
+// and 4.6 (of which about 2 are the launch).
+template <int N>
 __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ ws, int Hq, int Hkv, int G, int splits,
                                                      float *__restrict__ out)
 {
-    constexpr int CHUNK = 16;
-    static_assert(kMaxSplits <= 64 && kMaxSplits % CHUNK == 0, "one split per lane, whole chunks of them");
+    static_assert(kMaxSplits <= 64, "one split per lane");
     const int u = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
     const int b = u / Hkv, g = u - b * Hkv;
     const float *p = ws + ((int64_t)u * splits * G + h) * (D + 2);
     const int64_t stride = (int64_t)G * (D + 2);
-    f32x2_t x[CHUNK];
+    f32x2_t x[N];
     // past the last split: its partial again, read and then dropped (it may be
     // infinite, so a weight of 0 would not do)
-    auto load = [&](int s0) {
 #pragma unroll
-        for (int i = 0; i < CHUNK; ++i)
-            x[i] = *reinterpret_cast<const f32x2_t *>(p + min(s0 + i, splits - 1) * stride + 2 + 2 * lane);
-    };
+    for (int i = 0; i < N; ++i)
+        x[i] = *reinterpret_cast<const f32x2_t *>(p + min(i, splits - 1) * stride + 2 + 2 * lane);
     f32x2_t ml = {-INFINITY, 0.f};
     if (lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + lane * stride);
-    load(0);
     const float M = wave_max(ml.x);
     float lsum = 0.f;
     f32x2_t osum = {0.f, 0.f};
@@ -325,17 +322,12 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
         const float w = __builtin_amdgcn_exp2f(ml.x - M);  // 0 past the last split
         const float wl = w * ml.y;
 #pragma unroll
-        for (int s0 = 0; s0 < kMaxSplits; s0 += CHUNK) {
-            if (s0 >= splits) break;
-            if (s0 > 0) load(s0);
-#pragma unroll
-            for (int i = 0; i < CHUNK; ++i) {
-                const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s0 + i));
-                const bool in = s0 + i < splits;
-                lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), s0 + i));
-                osum.x += sc * (in ? x[i].x : 0.f);
-                osum.y += sc * (in ? x[i].y : 0.f);
-            }
+        for (int i = 0; i < N; ++i) {
+            const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i));
+            const bool in = i < splits;
+            lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), i));
+            osum.x += sc * (in ? x[i].x : 0.f);
+            osum.y += sc * (in ? x[i].y : 0.f);
         }
     }
     f32x2_t y = {0.f, 0.f};
@@ -461,7 +453,12 @@ extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, con
                scale_log2, sp.steps_per_split, out, ws);
     ss_status st = ss::check_launch("ss_sparse_attention");
     if (st != SS_OK || sp.splits == 1) return st;
-    combine_kernel<<<dim3(units, G), dim3(64), 0, s>>>(ws, Hq, Hkv, G, sp.splits, out);
+    // reads as many partials as there may be splits: 16 of them cost 2 splits of 88 units 0.6 us of 9.4
+    auto *combine = combine_kernel<kMaxSplits>;
+    if (sp.splits <= 4) combine = combine_kernel<4>;
+    else if (sp.splits <= 8) combine = combine_kernel<8>;
+    else if (sp.splits <= 16) combine = combine_kernel<16>;
+    combine<<<dim3(units, G), dim3(64), 0, s>>>(ws, Hq, Hkv, G, sp.splits, out);
     return ss::check_launch("ss_sparse_attention(combine)");
 }
 

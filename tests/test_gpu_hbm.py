@@ -700,12 +700,13 @@ def test_attention_with_less_workspace(ss, units, k, splits):
         assert float((out - got[0]).abs().max()) <= 2.0 ** -15 * float(kv.abs().max())
 
 
-@pytest.mark.parametrize("units,k,limit", [(8, 128, 32), (8, 128, 16), (8, 128, 8), (44, 256, 32), (1, 512, 32)])
+@pytest.mark.parametrize("units,k,limit", [(8, 128, 32), (8, 128, 16), (8, 128, 8), (44, 256, 32), (1, 512, 32),
+                                           (64, 128, 32), (128, 128, 32)])
 def test_attention_merge_keeps_infinities(ss, units, k, limit):
     """A channel whose 32-bit sums overflow is infinite in every split's
     partial, and so is the output: the merge multiplies no partial that it is
-    to leave out (0 * inf is no number).  19 splits, 16, 8, 5 and 32, on
-    either side of the 16 that are read at a time."""
+    to leave out (0 * inf is no number).  19 splits, 16, 8, 5, 32, 4 and 2 or
+    about as many, by kernels that read 4, 8, 16 or 32 partials."""
     G, blk, d = 4, 16, 128
     g = torch.Generator(device="cuda").manual_seed(units + limit)
     kv = torch.randn(units, k, 2, blk * d, generator=g, device="cuda").bfloat16()
