@@ -306,29 +306,30 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
     const int u = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
     const int b = u / Hkv, g = u - b * Hkv;
     const float *p = ws + ((int64_t)u * splits * G + h) * (D + 2);
-    const int64_t stride = (int64_t)G * (D + 2);
+    const int stride = G * (D + 2);
+    // partials past the last split read as zero (buffer bounds): a clamped one,
+    // weighted by 0, may be infinite, and selecting costs 0.2 us
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0,
+                                                                          ((splits - 1) * stride + D + 2) * 4, kBufferFlags);
     f32x2_t x[N];
-    // past the last split: its partial again, read and then dropped (it may be
-    // infinite, so a weight of 0 would not do)
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        x[i] = *reinterpret_cast<const f32x2_t *>(p + min(i, splits - 1) * stride + 2 + 2 * lane);
+        x[i] = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (i * stride + 2 + 2 * lane) * 4, 0, 0));
     f32x2_t ml = {-INFINITY, 0.f};
     if (lane < splits) ml = *reinterpret_cast<const f32x2_t *>(p + lane * stride);
     const float M = wave_max(ml.x);
+    // 0 past the last split, and everywhere if nothing is selected; no branch,
+    // behind which the partials' loads would move and wait for M (0.35 us)
+    const float w = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);
+    const float wl = w * ml.y;
     float lsum = 0.f;
     f32x2_t osum = {0.f, 0.f};
-    if (M != -INFINITY) {
-        const float w = __builtin_amdgcn_exp2f(ml.x - M);  // 0 past the last split
-        const float wl = w * ml.y;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i));
-            const bool in = i < splits;
-            lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), i));
-            osum.x += sc * (in ? x[i].x : 0.f);
-            osum.y += sc * (in ? x[i].y : 0.f);
-        }
+    for (int i = 0; i < N; ++i) {
+        const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i));
+        lsum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), i));
+        osum.x += sc * x[i].x;
+        osum.y += sc * x[i].y;
     }
     f32x2_t y = {0.f, 0.f};
     if (lsum > 0.f) y = f32x2_t{osum.x / lsum, osum.y / lsum};
