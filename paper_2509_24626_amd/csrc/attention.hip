@@ -37,6 +37,7 @@
 // split partials in split order.  All merges run in a fixed order, so results
 // do not depend on scheduling.  plan() says how waves and splits are chosen.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <unordered_map>
 
@@ -336,45 +337,73 @@ __global__ __launch_bounds__(64) void combine_kernel(const float *__restrict__ w
     *reinterpret_cast<f32x2_t *>(out + ((int64_t)b * Hq + g * G + h) * D + 2 * lane) = y;
 }
 
-// Waves per workgroup and splits per unit.
-//
-// One workgroup of 8 waves per unit writes the output itself, with no second
-// launch.  It is taken
-//   - below 32 steps (k * blk < 512 tokens), where splits would leave a wave
-//     one or two steps: 4 units of 16 steps 5.0 us against 5.7 with 4 waves
-//     and 7.1 with 4 splits of them; 64 of 24 steps 7.5 against 8.1 and 8.3;
-//   - up to 256 units, one per CU, where that is as fast as what the splits
-//     save: from 144 units at any length (160 units of 128 steps 29.3 us
-//     against 33.4, 192 units 32.4 against 41.6, 256 units 42.3 against 47.0),
-//     from 96 up to 96 steps (96 units of 64 steps 14.8 against 16.3, but of
-//     128 steps 25.6 against 24.0);
-//   - from 384 to 511 units, two rounds of the CUs (448 units of 128 steps
-//     71.9 us against 79.4 with two splits; 320 units 63.7 against 57.8).
-// Otherwise 4 waves, at least 4 steps a split (8 where there are more
-// workgroups than CUs), and the splits for which the fullest CU has least to
-// do: a step takes a CU about 0.32 us of the chip's bandwidth, a workgroup
-// costs about 0.012 us, the second launch 4 us (44 units of 256 steps: 5
-// splits 20.7 us, 12 splits 22.5; 264 units of 128 steps: 2 splits 56.5 us, 3
-// splits 52.8).  units * splits stays below 1024, which bounds the partials,
-// and no more than `most` splits are taken, for which there is room.
-split_plan plan(int units, int k, int blk, int most)
+// Waves of the workgroup that takes a whole unit: 8 where that is faster than
+// 4, us with 4 and with 8.  More waves share a unit's steps, but each brings a
+// partial to merge, and where the units fill the chip the steps share its
+// bandwidth anyway.
+//   - Below 8 steps the many heads' larger merge is shared by more threads: 1
+//     step of 256 units, G = 16, blocks of 32 4.7, 4.4; but G = 1 3.6, 3.8.  5 and 6
+//     steps are one round of 8 waves, two of 4 (1 unit, G = 1, blocks of 8 3.8, 3.6).
+//   - From 8 steps on blocks of 8 and 16 tokens, whose loads are shorter, gain
+//     with many heads (1 unit of 20 steps, G = 7, blocks of 8 6.3, 5.6; 160 units
+//     equal), with few heads only for few units (G = 1, blocks of 8: 1 unit of 20
+//     steps 6.2, 5.0; 16 7.0, 6.6; 128 equal, 256 9.5, 10.1); blocks of 32 lose 1 to 8%.
+//   - From 384 to 511 units, two rounds of the CUs, long selections gain with
+//     blocks of 32 (511 of 384 steps, G = 1 299, 288) and are equal otherwise;
+//     short ones lose (448 of 32 steps, G = 4 20.4, 21.7).
+int waves_of_one(int units, int steps, int G, int blk)
 {
+    if (units >= 384) return units < 512 && steps >= 96 ? 8 : 4;
+    if (units > 256) return 4;
+    if (steps < 8) {
+        if (G >= 3) return G >= 7 || steps < 7 || blk == 32 ? 8 : 4;
+        return steps >= 5 && steps <= 6 && blk < 32 && units <= 16 ? 8 : 4;
+    }
+    if (blk == 32 || steps == 8) return 4;  // 8 steps: two full rounds of 4 waves
+    if (G >= 7) return 8;
+    const int few = blk == 8 ? 128 : 64;
+    return units <= (G >= 3 ? few : few / 8) ? 8 : 4;
+}
+
+// Splits per unit: those that take least time by this model.  Its constants
+// (us, but for a common factor) are fitted so that the choices lose least
+// against the best of all plans over 6126 shapes (1 to 1024 units, 1 to 512
+// steps, G 1 to 16, every block size): 0.5% on average.  Two 4-wave workgroups
+// per CU lose 9%, up to a factor of 2.5 (few units of long selections); the
+// plan that gave units whole to 8 waves wherever it had won at 128 steps lost
+// 3%, up to a factor of 1.6 (us, then and now: 320 units of 64 steps 33.3,
+// 30.6; 112 of 64 15.1, 13.4; 448 of 32 21.9, 20.4).
+//   - The chip's bandwidth: kStepHbm per step and workgroup in flight.
+//   - The fullest CU: alone on it, a workgroup's 4 waves take a step each per
+//     round, of kRound (kLoad more for every other workgroup in flight);
+//     together, workgroups take kStep2 (two) or kStep3 per step each.
+//   - The second launch, with the partials' way through memory.
+// 24 steps at least, 4 a split; units * splits stays below 1024, which bounds
+// the partials, and no more than `most` splits are taken, for which there is
+// room.
+split_plan plan(int units, int k, int blk, int G, int most)
+{
+    constexpr float kStepHbm = 0.000945f, kRound = 0.197f, kLoad = 0.00018f, kStep2 = 0.2835f, kStep3 = 0.3245f;
+    constexpr float kMerge = 2.3f, kMergeSplit = 0.0077f, kMergeGroup = 0.00032f, kMergeHead = 0.00024f;
     const int steps = (int)(((int64_t)k * blk + TOK - 1) / TOK);
-    if ((units <= 256 && (steps < 32 || units >= 144 || (units >= 96 && steps <= 96))) ||
-        (units >= 384 && units < 512 && steps >= 32))
-        return {8, 1, steps};
     int best = 1;
     float least = 0.f;
-    for (int n = 1; n <= most && (n == 1 || (units * n < 1024 && n * (units * n <= CUS ? 4 : 8) <= steps)); ++n) {
-        const float rounds = (float)((units * n + CUS - 1) / CUS);
-        const float cost = rounds / n * steps * 0.32f + (n > 1 ? 0.012f * units * n + 4.f : 0.f);
+    for (int n = 1; n <= most && (n == 1 || (steps >= 24 && units * n < 1024 && 4 * n <= steps)); ++n) {
+        const int sps = (steps + n - 1) / n;
+        const float groups = (float)units * ((steps + sps - 1) / sps);  // workgroups: rounding may need fewer splits
+        const float rounds = std::ceil(groups / CUS);
+        const float cu = rounds == 1.f ? (float)((sps + 3) / 4 * 4) * (kRound + kLoad * groups)
+                                       : sps * rounds * (rounds == 2.f ? kStep2 : kStep3);
+        float cost = std::max(sps * groups * kStepHbm, cu);
+        if (n > 1) cost += kMerge + kMergeSplit * (groups / units) + (kMergeGroup + kMergeHead * G) * groups;
         if (n == 1 || cost < least) {
             best = n;
             least = cost;
         }
     }
     const int sps = (steps + best - 1) / best;
-    return {4, (steps + sps - 1) / sps, sps};
+    const int splits = (steps + sps - 1) / sps;
+    return {splits == 1 ? waves_of_one(units, steps, G, blk) : 4, splits, sps};
 }
 
 // The splits a workspace must have room for: two 4-wave workgroups per CU of
@@ -412,7 +441,7 @@ extern "C" size_t ss_sparse_attention_workspace(int B, int Hq, int Hkv, int d, i
 {
     if (!has_plan(B, Hq, Hkv, d, blk, k)) return 0;
     const int units = B * Hkv;
-    const int splits = std::max(least_splits(units, k, blk), plan(units, k, blk, kMaxSplits).splits);
+    const int splits = std::max(least_splits(units, k, blk), plan(units, k, blk, Hq / Hkv, kMaxSplits).splits);
     return splits > 1 ? splits * split_bytes(B, Hq) : 0;
 }
 
@@ -438,11 +467,11 @@ extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, con
     if (ws_bytes < need || (need && !workspace))
         return ss::fail(SS_ERR_OOM, "ss_sparse_attention: workspace %zu bytes < %zu", ws_bytes, need);
     const size_t room = workspace ? ws_bytes / split_bytes(B, Hq) : 0;
-    const split_plan sp = plan(units, k, blk, (int)std::min(room, (size_t)kMaxSplits));
+    const int G = Hq / Hkv;
+    const split_plan sp = plan(units, k, blk, G, (int)std::min(room, (size_t)kMaxSplits));
     hipStream_t s = ss::as_stream(stream);
     const float scale_log2 = scale * 1.4426950408889634f;
     const dim3 grid(units, sp.splits);
-    const int G = Hq / Hkv;
     const uint16_t *qq = static_cast<const uint16_t *>(q);
     const uint8_t *kv = static_cast<const uint8_t *>(kv_base);
     float *ws = static_cast<float *>(workspace);

@@ -673,6 +673,17 @@ def test_attention_launch_shapes(ss, units, G, blk, k):
     assert worst <= 2.0 ** -15 * float(kv.abs().max()), worst
 
 
+@pytest.mark.parametrize("units,G,blk,k", [(1, 1, 16, 5), (16, 2, 8, 11), (17, 2, 8, 10), (9, 3, 16, 7), (9, 3, 32, 3),
+                                           (300, 16, 8, 1), (4, 7, 8, 15), (8, 1, 16, 9), (9, 1, 16, 9),
+                                           (64, 4, 16, 10), (65, 4, 16, 10), (128, 4, 8, 25), (129, 4, 8, 25),
+                                           (200, 8, 16, 23), (200, 8, 16, 24), (3, 2, 16, 24), (2, 1, 32, 64),
+                                           (383, 1, 32, 48), (384, 1, 16, 95), (384, 1, 16, 96), (512, 1, 16, 96)])
+def test_attention_plan_lines(ss, units, G, blk, k):
+    """Either side of the lines between one workgroup of 4 and of 8 waves per
+    unit (by heads, block size, steps and units) and of the first splits."""
+    test_attention_launch_shapes(ss, units, G, blk, k)
+
+
 @pytest.mark.parametrize("units,k,splits", [(8, 128, 8), (4, 100, 7), (16, 511, 31), (24, 128, 8)])
 def test_attention_with_less_workspace(ss, units, k, splits):
     """A workspace smaller than the query's, down to the least one (two 4-wave

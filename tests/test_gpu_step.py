@@ -229,19 +229,19 @@ def test_groups_schedule_callback_error_and_checks(ss, resolve):
 @pytest.mark.parametrize("resolve", ["device", "host"])
 def test_steps_take_the_least_attention_workspace(ss, resolve):
     """A workspace of the least size per stream (two 4-wave workgroups a CU of
-    16 steps or more each: 8 splits of 24 units, of which the plan would use
-    10) serves the one-layer step and the groups schedule: the same
+    16 steps or more each: 8 splits of 8 units, of which the plan would use
+    more) serves the one-layer step and the groups schedule: the same
     selections, outputs that differ by the order of the splits' sums alone
     (every probability keeps 16 bits: 2^-15 of the largest |V|, six sigma of
     a scale of at most 2), and one byte less is refused."""
     from paper_2509_24626_amd import harness as H
-    cfg, seed = small_cfg(layers=2), 11
+    cfg, seed = small_cfg(B=4, layers=2), 11
     dev = resolve == "device"
     pa, A = build(cfg, seed, 4, dev)
     pb, Bm = build(cfg, seed, 4, dev)
     try:
-        one = 8 * 3 * cfg.Hq * 130 * 4
-        assert ss.ss_sparse_attention_workspace(3, cfg.Hq, cfg.Hkv, cfg.d, cfg.blk, cfg.k) > one
+        one = 8 * cfg.Hq * 130 * 4
+        assert ss.ss_sparse_attention_workspace(1, cfg.Hq, cfg.Hkv, cfg.d, cfg.blk, cfg.k) > one
         one = (one + 255) // 256 * 256
         for t in range(cfg.steps):
             qs = [H.query_stream(cfg, seed, l, cfg.steps)[t][1] for l in range(cfg.layers)]
