@@ -32,13 +32,36 @@
 // us for the first, 31.9, 32.4 and 41.4 against 31.4 for 20 x 8 x 512 to 4096.
 // Giving each XCD runs of 512 KiB left the first at 317 and slowed the ragged
 // ones to 205 and 42.
+//
+// Workgroups go to the XCDs in turn, so with the chunks of a row in their own
+// order and a power of two of them a row, one chunk of every row meets one XCD,
+// and what ragged rows leave out is left out on the same XCDs.  Rows of up to
+// 512 KiB of metadata therefore take their chunks in an order that differs from
+// row to row (spread(), a multiplicative hash of the row).  Plain order and
+// this, us: 512 sequences x 8 heads x 64 to 512 blocks 116, 94.6; 128 x 8 x 128
+// to 1024 56.0, 45.7; mean keys of 512 x 8 x 128 to 1024 130, 96.7.  Equal rows
+// pay for it, since each XCD then reads all over memory: 256 x 8 x 1024 160,
+// 163; 1024 x 8 x 512 319, 337.  In longer ragged rows the XCDs even out by
+// themselves (0 to 8% gained) and equal ones pay 3 to 6%; rows of an odd number
+// of chunks never meet the XCDs in step.
+//
+// Short rows by the hundred are bound by the workgroups that start, not by
+// HBM: one workgroup of four waves takes a whole row of up to 256 blocks, a
+// tile a wave at a time (wide()).  Rows of 33 to 64 blocks gain from 192 rows
+// on (two waves a workgroup and this, us: 32 x 8 x 48 3.5, 3.1; 128 rows 2.8,
+// 2.9), mean keys, whose rows take half the bytes, from 6144 rows on up to 256
+// blocks (6 to 8% at 8192 rows of 65, 0 to 6% at 192, 3% lost to 1% gained at
+// 250; with 2048 rows 0 to 16% lost).  Cuboid rows of 65 blocks and more are
+// bound by HBM and up to 30% slower so.
 #include "score_tile.hpp"
 
 namespace {
 
-constexpr int TILE = ss::kTile;  // one tile per wave
-constexpr int WAVES = 2;
-constexpr int BLOCKS_PER_WG = TILE * WAVES;
+constexpr int TILE = ss::kTile;
+constexpr int WAVES = 2, WIDE_WAVES = 4;  // waves of a workgroup
+constexpr int WIDE_TILES = 4;             // tiles of a wave in a wide workgroup, one otherwise
+constexpr int BLOCKS_PER_WG = TILE * WAVES, BLOCKS_PER_WIDE = TILE * WIDE_WAVES * WIDE_TILES;
+constexpr int kSpreadBytes = 512 * 1024;
 // Cuboid workgroups take 16.5 KiB of LDS, nine to a CU.  A launch that does
 // not fit at once reserves 22 KiB for each, seven to a CU: 64 x 8 x 8192 blocks
 // 317 us against 322, 32 x 8 x 8192 155 against 159 (six: 314 and 153, but 7.2
@@ -48,26 +71,66 @@ constexpr size_t kResidencyLds = 22 * 1024;
 constexpr int kResident = 9 * 256;
 constexpr size_t kStageBytes = (size_t)WAVES * ss::tile_shape<0>::STAGE * 16;
 
-template <int KIND, int AGG>
-__global__ __launch_bounds__(WAVES * 64) void score_kernel(const uint16_t *__restrict__ q,
-                                                           const uint8_t *__restrict__ meta,
-                                                           const int32_t *__restrict__ nblk, int u0, int Hq, int Hkv,
-                                                           int G, int nblk_max, int chunks_per_unit,
-                                                           float *__restrict__ scores)
+// Whether a workgroup of four waves takes a row.
+bool wide(int meta_kind, int64_t units, int nblk_max)
 {
-    __shared__ uint4 stage[WAVES][ss::tile_shape<KIND>::STAGE];
-    const int uc = blockIdx.x / chunks_per_unit;
-    const int u = u0 + uc, chunk = blockIdx.x - uc * chunks_per_unit;
-    const int b = u / Hkv, g = u - b * Hkv;
+    if (nblk_max <= BLOCKS_PER_WG) return false;
+    return units >= 192 && nblk_max <= 2 * BLOCKS_PER_WG ||
+           meta_kind == SS_META_MEAN && units >= 6144 && nblk_max <= BLOCKS_PER_WIDE;
+}
+
+// The bits of a chunk's number that differ from row to row: a permutation of
+// the row's chunks, since they come in whole groups of that many.
+int spread(int meta_kind, int chunks)
+{
+    const int bytes = BLOCKS_PER_WG * (meta_kind == SS_META_CUBOID ? ss::tile_shape<0>::ROW : ss::tile_shape<1>::ROW);
+    return chunks <= kSpreadBytes / bytes ? (chunks & -chunks) - 1 : 0;
+}
+
+// Division of 0 <= x < 2^31 by d, as a multiplication: with 2^(s-1) < d <= 2^s
+// and d*mul = 2^(31+s) + e, 0 <= e < 2^s, x*mul / 2^(31+s) exceeds x/d by less
+// than 1/d.  There is no instruction for it, and two divisions at the head of
+// every workgroup cost small calls up to 6% (mean keys of 64 to 128 rows of 48).
+struct Divisor {
+    uint32_t mul, shift;
+    explicit Divisor(int d) : shift(0)
+    {
+        while ((1ll << shift) < d) ++shift;
+        mul = (uint32_t)(((1ull << (31 + shift)) + d - 1) / d);
+    }
+    __device__ int divide(int x) const { return __umulhi(2u * x, mul) >> shift; }
+};
+
+template <int KIND, int AGG, int NW, int NT>
+__global__ __launch_bounds__(NW * 64) void score_kernel(const uint16_t *__restrict__ q,
+                                                        const uint8_t *__restrict__ meta,
+                                                        const int32_t *__restrict__ nblk, int u0, int Hq, int Hkv,
+                                                        Divisor by_hkv, int G, int nblk_max, int chunks_per_unit,
+                                                        Divisor by_chunks, int spread, float *__restrict__ scores)
+{
+    __shared__ uint4 stage[NW][ss::tile_shape<KIND>::STAGE];
+    const int uc = by_chunks.divide(blockIdx.x);
+    const int u = u0 + uc;
+    const int chunk = (blockIdx.x - uc * chunks_per_unit) ^ (((uint32_t)uc * 0x9E3779B1u >> 16) & spread);
+    const int b = by_hkv.divide(u), g = u - b * Hkv;
     int n = nblk[b];
     n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j0 = chunk * BLOCKS_PER_WG + wave * TILE;
-    if (j0 >= n) return;
-
     const int lane = threadIdx.x & 63;
-    const float v = ss::score_tile<KIND, AGG>(q, meta, b, g, u, n, j0, Hq, G, nblk_max, stage[wave]);
-    if (lane < TILE && j0 + lane < n) scores[(int64_t)u * nblk_max + j0 + lane] = v;
+    int j0 = chunk * (TILE * NW * NT) + wave * TILE;
+#pragma unroll
+    for (int t = 0; t < NT; ++t, j0 += TILE * NW) {
+        if (j0 >= n) return;
+        const float v = ss::score_tile<KIND, AGG>(q, meta, b, g, u, n, j0, Hq, G, nblk_max, stage[wave]);
+        if (lane < TILE && j0 + lane < n) scores[(int64_t)u * nblk_max + j0 + lane] = v;
+    }
+}
+
+template <int NW, int NT>
+auto pick(int meta_kind, int agg)
+{
+    if (meta_kind == SS_META_CUBOID) return agg == SS_AGG_MAX ? score_kernel<0, 0, NW, NT> : score_kernel<0, 1, NW, NT>;
+    return agg == SS_AGG_MAX ? score_kernel<1, 0, NW, NT> : score_kernel<1, 1, NW, NT>;
 }
 
 }  // namespace
@@ -77,25 +140,25 @@ namespace ss {
 ss_status launch_score(const void *q, const void *meta, int meta_kind, int agg, const int32_t *nblk, int B, int Hq,
                        int Hkv, int nblk_max, float *scores, hipStream_t s)
 {
-    const int chunks = (nblk_max + BLOCKS_PER_WG - 1) / BLOCKS_PER_WG;
     const int64_t units = (int64_t)B * Hkv;
+    const bool w = wide(meta_kind, units, nblk_max);
+    const int blocks = w ? BLOCKS_PER_WIDE : BLOCKS_PER_WG, threads = (w ? WIDE_WAVES : WAVES) * 64;
+    const int chunks = (nblk_max + blocks - 1) / blocks;
     if (units * chunks == 0) return SS_OK;
     // what one launch of 256 threads per 256 blocks holds is taken; these
     // shorter workgroups may need several launches for it
     SS_CHECK_SUPPORTED(units * ((nblk_max + 255) / 256) <= 0xFFFFFFFFll / 256, "score: grid too large");
-    const int64_t per = 0xFFFFFFFFll / (WAVES * 64) / chunks;  // units per launch
+    const int64_t per = 0xFFFFFFFFll / threads / chunks;  // units per launch
     const auto *qq = static_cast<const uint16_t *>(q);
     const auto *mm = static_cast<const uint8_t *>(meta);
-    const dim3 bl(WAVES * 64);
     const int G = Hq / Hkv;
-    auto *kernel = score_kernel<0, 0>;
-    if (meta_kind == SS_META_CUBOID) kernel = agg == SS_AGG_MAX ? score_kernel<0, 0> : score_kernel<0, 1>;
-    else kernel = agg == SS_AGG_MAX ? score_kernel<1, 0> : score_kernel<1, 1>;
+    auto *kernel = w ? pick<WIDE_WAVES, WIDE_TILES>(meta_kind, agg) : pick<WAVES, 1>(meta_kind, agg);
     for (int64_t u0 = 0; u0 < units; u0 += per) {
         const int64_t grid = (units - u0 < per ? units - u0 : per) * chunks;
-        const bool cap = meta_kind == SS_META_CUBOID && grid > kResident;
-        ss::launch_lds(kernel, dim3((unsigned)grid), bl, cap ? kResidencyLds - kStageBytes : 0, s, qq, mm, nblk, (int)u0,
-                       Hq, Hkv, G, nblk_max, chunks, scores);
+        const bool cap = !w && meta_kind == SS_META_CUBOID && grid > kResident;
+        ss::launch_lds(kernel, dim3((unsigned)grid), dim3(threads), cap ? kResidencyLds - kStageBytes : 0, s, qq, mm,
+                       nblk, (int)u0, Hq, Hkv, Divisor(Hkv), G, nblk_max, chunks, Divisor(chunks),
+                       spread(meta_kind, chunks), scores);
     }
     return check_launch("ss_score_blocks");
 }

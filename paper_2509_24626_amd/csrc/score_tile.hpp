@@ -48,6 +48,13 @@ __device__ __forceinline__ float score_tile(const uint16_t *__restrict__ q, cons
     const int L = lane >> 4;
     const int col = lane & 15;
 
+    // channel chunks of head g*G + col: 4*m + L for m < 4
+    const bool live = col < G;
+    const uint16_t *qh = q + ((int64_t)b * Hq + g * G + (live ? col : 0)) * D;
+    uint4 x[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) x[m] = *reinterpret_cast<const uint4 *>(qh + (4 * m + L) * 8);
+
     const uint8_t *mu = meta + (int64_t)u * nblk_max * S::ROW;
     // n * S::ROW <= kMaxBlocks * 512 bytes < 2^31
     const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc((void *)mu, (short)0, n * S::ROW, kMetaBufferFlags);
@@ -56,20 +63,21 @@ __device__ __forceinline__ float score_tile(const uint16_t *__restrict__ q, cons
     for (int i = 0; i < S::NLD; ++i)  // rows at or past n read as zero (buffer bounds) and are not stored
         r[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                              mrs, (uint32_t)j0 * S::ROW + lane * 16 + i * 1024, 0, kMetaStream));
+    // nothing is made of q before every row has been asked for, or the compiler
+    // puts its wait for q in front of some of them: 3 to 11% slower
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) asm volatile("" : "+v"(x[m].x), "+v"(x[m].y), "+v"(x[m].z), "+v"(x[m].w));
 
     // weights of head g*G + col for chunks 4*m + L, selected branch-free with
     // masks on the 32-bit words (two bf16 each)
     frag_t w[S::NCH];
     {
-        const bool live = col < G;
-        const uint16_t *qh = q + ((int64_t)b * Hq + g * G + (live ? col : 0)) * D;
         const uint32_t live_mask = live ? 0xFFFFFFFFu : 0u;
 #pragma unroll
         for (int m = 0; m < S::NCH; ++m) {
             const bool hi_half = KIND == 0 && m >= 4;  // cuboid chunks 16..31 multiply hi
-            const int c = (4 * m + L) & 15;            // q channels c*8 .. c*8+7
-            const uint4 x = *reinterpret_cast<const uint4 *>(qh + c * 8);
-            uint32_t v[4] = {x.x, x.y, x.z, x.w};
+            uint32_t v[4] = {x[m & 3].x, x[m & 3].y, x[m & 3].z, x[m & 3].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t keep = live_mask;
@@ -82,6 +90,7 @@ __device__ __forceinline__ float score_tile(const uint16_t *__restrict__ q, cons
             w[m].u = make_uint4(v[0], v[1], v[2], v[3]);
         }
     }
+    __builtin_amdgcn_sched_barrier(0);  // ... and all of this is done before the first row is waited for
 
 #pragma unroll
     for (int i = 0; i < S::NLD; ++i) {

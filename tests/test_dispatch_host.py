@@ -94,7 +94,8 @@ def test_score_launch_limits(stand_in, B, Hkv, n, taken):
         if taken:
             assert all(0 < x * threads < 1 << 32 for x, _, _, threads in shapes), (name, shapes)
             if name != "topk":
-                assert sum(x for x, _, _, _ in shapes) == units * (-(-n // 32)), (name, shapes)
+                blocks = {128: 32, 256: 256}[shapes[0][3]]  # a workgroup's
+                assert sum(x for x, _, _, _ in shapes) == units * (-(-n // blocks)), (name, shapes)
             else:
                 assert shapes[-1][0] == units, shapes
 

@@ -771,6 +771,21 @@ def test_score_tile_edges(ss, kind, agg, nblk, G):
         assert bool((scores[b, :, k:] == 7.5).all())
 
 
+@pytest.mark.parametrize("kind,agg", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("B,n", [(95, 64), (96, 32), (96, 33), (97, 63), (96, 64), (96, 65), (3071, 256), (3072, 65),
+                                 (3073, 129), (3072, 256), (3072, 257), (5, 1023), (300, 100), (37, 192), (40, 639),
+                                 (9, 1024), (9, 1025), (9, 2048), (9, 2049)])
+def test_score_rows_of_any_length(ss, kind, agg, B, n):
+    """Rows of lengths from nothing to all, two heads a sequence, on either
+    side of the numbers of rows (192, 6144) and blocks (33 to 64, 256) from
+    which one workgroup takes a row, and rows of 4, 6, 20, 32, 33, 64 and 65
+    chunks, which are taken in an order that differs from row to row up to 32
+    (mean keys: 64)."""
+    nblk = torch.randint(0, n + 1, (B,), generator=torch.Generator().manual_seed(B + n)).tolist()
+    nblk[0], nblk[1], nblk[-1] = n, 0, n - 1
+    test_score_tile_edges(ss, kind, agg, tuple(nblk), 4)
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257])
 @pytest.mark.parametrize("B,Hkv,G", [(3, 2, 4), (64, 4, 1), (257, 1, 7), (2, 1, 16)])
 def test_score_topk_in_one_launch(ss, n, B, Hkv, G):
