@@ -5,8 +5,8 @@
 // unsigned order is the float order (-0 folded onto +0; key 0, below every
 // score, for padding).  Wave w owns R*64 consecutive scores, lane l of it the
 // scores i*64 + l of those: the loads are coalesced, are issued before the
-// unit's block count arrives (the row holds nblk_max scores, so every load is
-// in bounds), and ranks in block order are ballots.
+// unit's block count arrives (loads past the row's nblk_max scores read as
+// zero, by the bounds of its buffer), and ranks in block order are ballots.
 //
 // The selection is every key above a bound and the first `quota` keys equal
 // to it.  To find the bound (m = min(k, n) keys wanted):
@@ -160,7 +160,7 @@ __device__ __forceinline__ void key_range(const uint32_t (&key)[R], uint32_t &lo
 
 template <int NW, int R>
 struct place_t {
-    unsigned long long map[2][NW][R];
+    alignas(8) uint32_t map[2][NW][2 * R];  // a bit per score
     int tot[2][NW];
 };
 
@@ -184,14 +184,17 @@ __device__ __forceinline__ void place(const uint32_t (&key)[R], bound_t bound, i
             hi = lane == i ? (uint32_t)(mask >> 32) : hi;
             c += __popcll(mask);
         }
-        if (lane < R) sm.map[which][wave][lane] = (unsigned long long)hi << 32 | lo;
+        uint32_t *map = sm.map[which][wave];
+        if (lane < R) {
+            map[2 * lane] = lo;
+            map[2 * lane + 1] = hi;
+        }
         if (lane == 0) sm.tot[which][wave] = c;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if constexpr (R == 64) {
-            return sm.map[which][wave][lane];
+            return (unsigned long long)map[2 * lane + 1] << 32 | map[2 * lane];
         } else {
-            const uint32_t w = reinterpret_cast<const uint32_t *>(sm.map[which][wave])[lane * R / 32];
-            return (w >> (lane * R % 32)) & ((1u << R) - 1u);
+            return (map[lane * R / 32] >> (lane * R % 32)) & ((1u << R) - 1u);
         }
     };
     bits_t bits = hand_over(0, [&](uint32_t x) { return x > bound.above; }), eq_bits = 0;
