@@ -143,13 +143,17 @@ def _stream(s):
     if s is None:
         # Called for every launch: torch.cuda.current_stream() builds a Stream
         # object and asks for the device count each time (3.6 us a call, more
-        # than a kernel launch); the raw handle of the same stream costs 0.3.
+        # than a kernel launch); the raw handle of the same stream costs 0.3
+        # where this torch has the two functions behind it.
         global _torch
         if _torch is None:
             import torch
             _torch = torch
         if _torch.cuda.is_initialized():
-            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+            try:
+                return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return _torch.cuda.current_stream().cuda_stream if _torch.cuda.is_available() else None
     if isinstance(s, int):
         return s

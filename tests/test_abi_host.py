@@ -109,6 +109,19 @@ def test_attention_workspace_sizes():
            FAKE, w - 1, 0)
 
 
+def test_stream_without_the_raw_functions(monkeypatch):
+    """A torch that lacks the two private functions behind the current
+    stream's raw handle gives it through its public object."""
+    from types import SimpleNamespace as N
+    cuda = N(is_initialized=lambda: True, is_available=lambda: True, current_stream=lambda: N(cuda_stream=7))
+    for c in (N(), N(_cuda_getDevice=lambda: 0)):
+        monkeypatch.setattr(ss, "_torch", N(_C=c, cuda=cuda))
+        assert ss._stream(None) == 7
+    raw = N(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: d + 2)
+    monkeypatch.setattr(ss, "_torch", N(_C=raw, cuda=cuda))
+    assert ss._stream(None) == 5
+
+
 def test_host_alloc_rejects_bad_flags():
     expect(ss.SS_ERR_INVALID_ARG, ss.ss_host_alloc_mapped, 4096, 7)
     assert ss.ss_host_alloc_mapped(0) == (0, 0)
