@@ -57,6 +57,25 @@ def test_attention_takes_every_workspace_size(stand_in):
     assert fewer > 10  # the shapes reach plans with more splits than the least size holds
 
 
+SPLITS = r"""
+P, got = 0x1000, []
+for B, Hq, Hkv, blk, k in json.loads(sys.argv[2]):
+    n = ss.ss_sparse_attention_workspace(B, Hq, Hkv, 128, blk, k)
+    ss.ss_sparse_attention(P, P, P, P, P, 300, B, Hq, Hkv, 128, blk, k, 0.1, P, P if n else None, n, stream=0)
+    got.append(launches())
+print(json.dumps(got))
+"""
+
+
+def test_shapes_of_the_scratch_tests_split(stand_in):
+    """The shapes that test_zz_no_alloc.py runs to fill the static scratch,
+    which takes the plan of its full workspace: a launch of units x splits
+    workgroups and the merge; and the one that runs without."""
+    made = json.loads(hip_stand_in.run(stand_in, SPLITS, json.dumps([(2, 32, 8, 16, 128), (1, 8, 2, 16, 64),
+                                                                     (64, 32, 8, 16, 8)])))
+    assert [x[0][:2] for x in made] == [[16, 16], [2, 16], [512, 1]] and [len(x) for x in made] == [2, 2, 1], made
+
+
 SCORE = r"""
 P, got = 0x1000, []
 for B, Hkv, n in json.loads(sys.argv[2]):

@@ -217,7 +217,7 @@ def test_save_runs_and_chunks(ss, oracle_impl, blk, Hkv, lens, n_new, threads, s
     16-byte aligned (`shift`); bytes outside the saved tokens are untouched."""
     from paper_2509_24626_amd import harness as H
     B, rb = len(lens), 2 * blk * D * 2
-    blocks = max(lens) // blk + n_new // blk + 2
+    blocks = (max(lens) + 4 * n_new) // blk + 1
     pool = H.HostPool(B * Hkv * blocks * rb + 16)
     pool.u8[:] = np.frombuffer(np.random.default_rng(blk + n_new).bytes(pool.nbytes), np.uint8)
     want = pool.u8.copy()
@@ -225,12 +225,20 @@ def test_save_runs_and_chunks(ss, oracle_impl, blk, Hkv, lens, n_new, threads, s
     cap = np.full(B, blocks, np.int32)
     saver = ss.ss_kv_saver_create(B, Hkv, blk, D, pool.host, off, cap, n_new, 2, threads)
     try:
-        for s in range(3):  # the third save waits for the first one's staging buffer
+        for s in range(3):
             kv = bf16_bits((B, n_new, Hkv, 2, D), torch.Generator().manual_seed(100 * s + blk))
             ss.ss_kv_save(saver, torch.from_numpy(kv.view(np.int16)).cuda(), n_new, np.asarray(lens, np.int32))
             ss.ss_kv_save_wait(saver)
             oracle_impl.save(kv, np.asarray(lens, np.int32), blk, want, off, cap)
             np.testing.assert_array_equal(pool.u8, want)
+        kvs = [bf16_bits((B, n_new, Hkv, 2, D), torch.Generator().manual_seed(100 * s + blk)) for s in (3, 4, 5, 6)]
+        new = [torch.from_numpy(kv.view(np.int16)).cuda() for kv in kvs]
+        for s in range(4):  # no wait between them: the third save waits for the first one's staging buffer
+            ss.ss_kv_save(saver, new[s], n_new, np.asarray(lens, np.int32) + s * n_new)
+        ss.ss_kv_save_wait(saver)
+        for s in range(4):
+            oracle_impl.save(kvs[s], np.asarray(lens, np.int32) + s * n_new, blk, want, off, cap)
+        np.testing.assert_array_equal(pool.u8, want)
     finally:
         ss.ss_kv_saver_destroy(saver)
         pool.close()

@@ -7,7 +7,8 @@ sanitized builds of the library and of the oracle.  ThreadSanitizer: the
 tests that drive the resolve pool and the working-set tracker's workers.
 The builds come from paper_2509_24626_amd/build_sanitized.py (host code
 instrumented, the gfx950 kernels built as usual).  The FlashD2H saver's
-threads wait on HIP copies, so they need a GPU and are not covered here."""
+threads wait on HIP copies, so they need a GPU and are not covered here;
+test_save_host.py runs them on the CPU, against a stand-in, without a sanitizer."""
 import os
 import subprocess
 import sys

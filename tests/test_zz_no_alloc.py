@@ -37,9 +37,9 @@ def _attend_both(ss, w, slots, cap, slot_limit):
 @pytest.mark.parametrize("order", ["large-then-small", "small-then-large"])
 def test_static_scratch_matches_workspace_entry_point(ss, oracle_impl, order):
     """Shapes that split the selection over several workgroups per unit, so
-    the partials go through the scratch array: 16 units x 8 splits, then 2
-    units x 4 splits (and the reverse order), each against the workspace
-    entry point and the oracle."""
+    the partials go through the scratch array: 16 units, then 2 units, of 16
+    splits each (and the reverse order; test_dispatch_host.py holds the launch
+    to that), each against the workspace entry point and the oracle."""
     shapes = [(2, 32, 8, 16, 300, 128, "large"), (1, 8, 2, 16, 80, 64, "small")]
     if order == "small-then-large":
         shapes = shapes[::-1]
