@@ -495,7 +495,8 @@ extern "C" ss_status ss_sparse_attention(const void *q, const void *kv_base, con
 // ------------------------------------------------- allocation-free variant
 // The split partials of ss_sparse_attention_static live in this file-scope
 // device array instead of a caller workspace.  Every supported shape fits:
-// with more than one split, units * splits <= 1023 and G <= 16, so the partials take at most 1023 * 16 * (128 + 2) * 4 bytes.
+// with more than one split, units * splits <= 1023 and G <= 16, so the partials
+// take at most 1023 * 16 * (128 + 2) * 4 bytes.
 // Host code never uses the array's name as an address: each device's copy
 // is looked up once with hipGetSymbolAddress and that pointer is passed on.
 namespace {

@@ -11,10 +11,11 @@
 // the next; the threads share each chunk's rows.  Staging buffers form a ring;
 // a save whose buffer is still being scattered waits for it.
 //
-// A copy with its event costs about 15 us on top of its bytes (33.5 MB in 32
-// copies took 1069 us with nothing scattered, in 8 copies 724), and what is
-// left after the last copy is the last chunk's scatter, at some 60 GB/s over 8
-// threads, so S bytes are copied in about sqrt(S / (60 GB/s * 15 us)) chunks.
+// A copy with its event costs about 15 us on top of its bytes (33.5 MB in one
+// copy 607 us with nothing scattered, in 5 662, in 8 709, in 32 1048), and what
+// is left after the last copy is the last chunk's scatter, at some 60 GB/s over
+// 8 threads, so S bytes are copied in about sqrt(S / (60 GB/s * 15 us)) chunks:
+// 33.5 MB in 5, less than 4 MiB in one.
 // The scatter turns 8 tokens x 8 channels of V at a time in registers and
 // stores whole lines past the caches; V value by value it was the slower side
 // of the pair.  8192 tokens x 8
