@@ -786,6 +786,27 @@ def test_score_rows_of_any_length(ss, kind, agg, B, n):
     test_score_tile_edges(ss, kind, agg, tuple(nblk), 4)
 
 
+@pytest.mark.parametrize("kind,agg", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("B,Hkv,n", [(17, 7, 1000), (29, 7, 50), (13, 5, 700), (9, 3, 224), (11, 12, 1024), (1, 11, 96),
+                                     (1000, 7, 70)])
+def test_score_batch_matches_single_rows(ss, kind, agg, B, Hkv, n):
+    """Heads and chunks a row in numbers that are no powers of two, rows that
+    one workgroup takes and chunks in another order, against a call for each
+    row by itself, which has none of them: bit for bit."""
+    G, d = 3, 128
+    g = torch.Generator(device="cuda").manual_seed(B + n)
+    meta = torch.randn(B, Hkv, n, 2 - kind, d, generator=g, device="cuda").bfloat16()
+    q = torch.randn(B, Hkv, G, d, generator=g, device="cuda").bfloat16()
+    nb = torch.randint(0, n + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    got, want = (torch.full((B, Hkv, n), 7.5, device="cuda") for _ in range(2))
+    print(f"[gpu] scores of {B} x {Hkv} rows of {n}, kind {kind}", flush=True)
+    ss.ss_score_blocks_variant(q, meta, kind, agg, nb, B, Hkv * G, Hkv, n, d, got)
+    for b in range(0, B, max(1, B // 30)):
+        for h in range(Hkv):
+            ss.ss_score_blocks_variant(q[b, h], meta[b, h], kind, agg, nb[b:], 1, G, 1, n, d, want[b, h])
+        assert torch.equal(got[b], want[b]), b
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257])
 @pytest.mark.parametrize("B,Hkv,G", [(3, 2, 4), (64, 4, 1), (257, 1, 7), (2, 1, 16)])
 def test_score_topk_in_one_launch(ss, n, B, Hkv, G):
