@@ -37,13 +37,16 @@
 // order and a power of two of them a row, one chunk of every row meets one XCD,
 // and what ragged rows leave out is left out on the same XCDs.  Rows of up to
 // 512 KiB of metadata therefore take their chunks in an order that differs from
-// row to row (spread(), a multiplicative hash of the row).  Plain order and
-// this, us: 512 sequences x 8 heads x 64 to 512 blocks 116, 94.6; 128 x 8 x 128
-// to 1024 56.0, 45.7; mean keys of 512 x 8 x 128 to 1024 130, 96.7.  Equal rows
-// pay for it, since each XCD then reads all over memory: 256 x 8 x 1024 160,
-// 163; 1024 x 8 x 512 319, 337.  In longer ragged rows the XCDs even out by
-// themselves (0 to 8% gained) and equal ones pay 3 to 6%; rows of an odd number
-// of chunks never meet the XCDs in step.
+// row to row (spread(), a multiplicative hash), for cuboids from one run of 32
+// rows to the next.  Plain order and this, us: 512 sequences x 8 heads x 64 to
+// 512 blocks 118, 93; 128 x 8 x 128 to 1024 55.5, 47.6; mean keys of 512 x 8 x
+// 128 to 1024 129, 96.5.  Equal rows are best read with each XCD in a part of
+// memory of its own, which a run keeps: 1024 x 8 x 512 319, 321, but 337 with an
+// order a row, and 163 against 160 for 256 x 8 x 1024.  Mean keys pay 0 to 5%
+// with an order a row and up to 7% with runs (2048 rows of 128), which also even
+// out their ragged rows less.  In longer rows the XCDs even out by themselves
+// (0 to 8% gained) and equal ones pay 3 to 6%; rows of an odd number of chunks
+// never meet the XCDs in step.
 //
 // Short rows by the hundred are bound by the workgroups that start, not by
 // HBM: one workgroup of four waves takes a whole row of up to 256 blocks, a
@@ -62,6 +65,8 @@ constexpr int WAVES = 2, WIDE_WAVES = 4;  // waves of a workgroup
 constexpr int WIDE_TILES = 4;             // tiles of a wave in a wide workgroup, one otherwise
 constexpr int BLOCKS_PER_WG = TILE * WAVES, BLOCKS_PER_WIDE = TILE * WIDE_WAVES * WIDE_TILES;
 constexpr int kSpreadBytes = 512 * 1024;
+// runs of 16 rows: equal rows up to 6% slower; of 64: ragged ones lose up to half the gain
+constexpr int kRunLog2 = 5;
 // Cuboid workgroups take 16.5 KiB of LDS, nine to a CU.  A launch that does
 // not fit at once reserves 22 KiB for each, seven to a CU: 64 x 8 x 8192 blocks
 // 317 us against 322, 32 x 8 x 8192 155 against 159 (six: 314 and 153, but 7.2
@@ -111,7 +116,8 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const uint16_t *__restri
     __shared__ uint4 stage[NW][ss::tile_shape<KIND>::STAGE];
     const int uc = by_chunks.divide(blockIdx.x);
     const int u = u0 + uc;
-    const int chunk = (blockIdx.x - uc * chunks_per_unit) ^ (((uint32_t)uc * 0x9E3779B1u >> 16) & spread);
+    const uint32_t run = (uint32_t)uc >> (KIND == 0 ? kRunLog2 : 0);  // rows that share an order
+    const int chunk = (blockIdx.x - uc * chunks_per_unit) ^ ((run * 0x9E3779B1u >> 16) & spread);
     const int b = by_hkv.divide(u), g = u - b * Hkv;
     int n = nblk[b];
     n = n < 0 ? 0 : (n > nblk_max ? nblk_max : n);

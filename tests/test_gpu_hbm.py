@@ -774,7 +774,7 @@ def test_score_tile_edges(ss, kind, agg, nblk, G):
 @pytest.mark.parametrize("kind,agg", [(0, 0), (1, 1)])
 @pytest.mark.parametrize("B,n", [(95, 64), (96, 32), (96, 33), (97, 63), (96, 64), (96, 65), (3071, 256), (3072, 65),
                                  (3073, 129), (3072, 256), (3072, 257), (5, 1023), (300, 100), (37, 192), (40, 639),
-                                 (9, 1024), (9, 1025), (9, 2048), (9, 2049)])
+                                 (9, 1024), (70, 1024), (9, 1025), (9, 2048), (9, 2049)])
 def test_score_rows_of_any_length(ss, kind, agg, B, n):
     """Rows of lengths from nothing to all, two heads a sequence, on either
     side of the numbers of rows (192, 6144) and blocks (33 to 64, 256) from
