@@ -248,7 +248,9 @@ __global__ __launch_bounds__(NT, R == 16 ? 8 : 1) void topk_kernel(const float *
     __shared__ __align__(16) int count[NW > 1 ? kCopies * kPitch : 4];
     auto clear = [&] {
         int4 *z = reinterpret_cast<int4 *>(count);
-        for (int i = t; i < kCopies * kPitch / 4; i += NT) z[i] = make_int4(0, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kCopies * kPitch / 4; i += NT)  // no counter a lane, for which R = 16 had no register left
+            if (i + t < kCopies * kPitch / 4) z[i + t] = make_int4(0, 0, 0, 0);
     };
     if constexpr (NW > 1) clear();
     int n = nblk[b];
