@@ -674,13 +674,13 @@ KERNEL_SOURCES = {
 # 2,4,10,20,18,8,2, host resolve
 _KEY = ["hier-b64-ctx128k-blk16-k128-cache25", 0, 20, [2, 4, 10, 20, 18, 8, 2], "host"]
 TRAFFIC = {
-    "gather": {"key": _KEY, "digest": "8fb62684d8faca19", "bytes": 245799178, "fetch": 123711754,
+    "gather": {"key": _KEY, "digest": "8fb62684d8faca19", "bytes": 245799191, "fetch": 123711767,
               "write": 122087424},
     "score": {"key": _KEY, "digest": "2e132a6e12c33d33", "bytes": 2168457120, "fetch": 2151679904,
               "write": 16777216},
-    "topk": {"key": _KEY, "digest": "3c916fdb6cb0a067", "bytes": 18219005, "fetch": 16908285,
-              "write": 1310720},
-    "attention": {"key": _KEY, "digest": "16eef85aba2da811", "bytes": 539155620, "fetch": 538107044,
+    "topk": {"key": _KEY, "digest": "e7aa311a24bebe16", "bytes": 17170301, "fetch": 16908157,
+              "write": 262144},
+    "attention": {"key": _KEY, "digest": "16eef85aba2da811", "bytes": 539155428, "fetch": 538106852,
               "write": 1048576},
 }
 
